@@ -198,6 +198,7 @@ size_t btc_aq_workspace_bytes(const btc_shape* s, int32_t M) {
   size_t need = aq::align256((size_t)rows * s->in * 2) + aq::align256((size_t)rows * s->out * 4) + aq::align256(inner);
   // many rows: the sign matrix as int8 and the sums of the code rows, for the integer matrix cores
   const Dims d = dims_of(*s);
+  if (gemm_decode_i8_covers(d, M)) need = std::max(need, aq::align256(gemm_decode_i8_workspace_bytes(d, M)));
   if (gemm_wide_i8_covers(d, M)) need = std::max(need, aq::align256(gemm_wide_i8_workspace_bytes(d, M)));
   return need;
 }
@@ -242,6 +243,14 @@ btc_status btc_gemm_aq(void* stream, const btc_shape* s, const uint32_t* packed,
   hipStream_t q = (hipStream_t)stream;
   {
     const Dims d = dims_of(*s);
+#ifdef BTC_PLAN_ENV
+    if (const char* e = getenv("BTC_ROUTE")) {
+      if (e[0] == 'w') return gemm_wide_i8(q, d, packed, codebook, alpha, mu, wsum, Q, lo, step, M, Y, (int)y_dtype, workspace, workspace_bytes);
+    }
+#endif
+    if (M > 16 && gemm_decode_i8_covers(d, M))
+      return gemm_decode_i8(q, d, packed, codebook, alpha, mu, wsum, Q, lo, step, M, Y, (int)y_dtype, workspace,
+                            workspace_bytes);
     if (gemm_wide_i8_covers(d, M))   // enough rows to fill the chip: int8 operands on the integer matrix cores
       return gemm_wide_i8(q, d, packed, codebook, alpha, mu, wsum, Q, lo, step, M, Y, (int)y_dtype, workspace,
                           workspace_bytes);

@@ -57,24 +57,20 @@ size_t btc_workspace_bytes(const btc_shape* s, int32_t rows, int is_gemm) {
   const btc::Dims d = btc::dims_of(*s);
   if (is_gemm) {
     need += (((size_t)rows * sizeof(float)) + 15) & ~(size_t)15;  // fp32 row sums of X
-    // partial sums of a call that the tiled contraction kernel splits along k
-    if (btc::gemm_tiled_covers(d, rows)) need = std::max(need, btc::gemm_tiled_workspace_bytes(d, rows));
-    // the sign matrix as bytes, for calls with many rows
+    // partial sums of a call that the decoding contraction kernel splits along k, or its row sums
+    if (btc::gemm_decode_covers(d, rows)) need = std::max(need, btc::gemm_decode_workspace_bytes(d, rows));
+    // the sign matrix as bytes, for calls with many rows on other settings
     if (btc::gemm_wide_covers(d, rows)) need = std::max(need, btc::gemm_wide_workspace_bytes(d, rows));
     if (btc::gemm_rows_covers(d, rows)) need = std::max(need, btc::gemm_rows_workspace_bytes(d, rows));
-    if (rows > 64 && rows <= 128 && btc::gemm_rows_covers(d, 64)) {   // may run as 64 rows + the rest
-      need = std::max(need, btc::gemm_rows_workspace_bytes(d, 64));
-      if (btc::gemv_mfma_covers(d, 16)) need = std::max(need, btc::gemv_mfma_workspace_bytes(d, 16));
-    }
     // a call with few rows may go to the decode engine, 16 rows at a time
     if (rows <= 64 && btc::gemv_mfma_covers(d, rows < 16 ? rows : 16))
       need = std::max(need, btc::gemv_mfma_workspace_bytes(d, rows < 16 ? rows : 16));
   } else {
     // the table engine's slots (zero between calls), then the partial sums of a batched call
-    // that goes to the tiled contraction kernel and is split along k
+    // that goes to the decoding contraction kernel and is split along k
     need = btc::gemv_table_region_bytes(d);
     size_t extra = 0;
-    if (rows > 1 && btc::gemm_tiled_covers(d, rows)) extra = btc::gemm_tiled_workspace_bytes(d, rows);
+    if (btc::gemm_decode_covers(d, rows)) extra = btc::gemm_decode_workspace_bytes(d, rows);
     if (btc::gemv_mfma_covers(d, rows)) extra = std::max(extra, btc::gemv_mfma_workspace_bytes(d, rows));
     need += extra;
   }

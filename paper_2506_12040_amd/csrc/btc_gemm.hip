@@ -73,35 +73,22 @@ btc_status btc_gemm(void* stream, const btc_shape* s, const uint32_t* packed, co
   const Dims d = dims_of(*s);
   float* rowsum = (float*)((char*)workspace + 16);
   const int is_bf16 = x_dtype == BTC_BF16;
+#ifdef BTC_PLAN_ENV
+  if (const char* e = getenv("BTC_ROUTE")) {
+    if (e[0] == 'd') return gemm_decode(q, d, packed, codebook, alpha, mu, X, is_bf16, M, Y, (int)y_dtype, workspace, workspace_bytes, 0);
+    if (e[0] == 'w') return gemm_wide(q, d, packed, codebook, alpha, mu, X, is_bf16, M, Y, (int)y_dtype, workspace, workspace_bytes);
+  }
+#endif
+  const double decode_us = gemm_decode_covers(d, M) ? gemm_decode_estimate_us(d, M) : 1e30;
   // 17..64 activation rows: the same operand scheme with two or four blocks of activation rows
   // per table read, one pass over the index stream.
-  if (gemm_rows_covers(d, M) &&
-      gemm_rows_estimate_us(d, M) < (gemm_tiled_covers(d, M) ? gemm_tiled_estimate_us(d, M) : 1e30))
+  if (gemm_rows_covers(d, M) && gemm_rows_estimate_us(d, M) < decode_us)
     return gemm_rows(q, d, packed, codebook, alpha, mu, X, is_bf16, M, Y, (int)y_dtype, workspace);
-  // 65..128 rows on a large matrix (6 MB of indices or more): two passes of that kernel (64 rows, then
-  // the rest) still beat a 256-row tile that is half empty (8192 x 28672, M = 96: 77 against 118 us); the
-  // estimates decide.
-  if (M > 64 && M <= 128 && (long long)d.out * d.wpr * 4 >= (6LL << 20) && gemm_rows_covers(d, 64) &&
-      gemm_tiled_covers(d, M)) {
-    const int rest = M - 64;
-    const double est = gemm_rows_estimate_us(d, 64) +
-                       (rest >= 17 ? gemm_rows_estimate_us(d, rest) : gemv_mfma_estimate_us(d, rest));
-    if (1.1 * est < gemm_tiled_estimate_us(d, M)) {
-      const size_t ysz = y_dtype == BTC_F32 ? 4 : 2;
-      st = gemm_rows(q, d, packed, codebook, alpha, mu, X, is_bf16, 64, Y, (int)y_dtype, workspace);
-      if (st != BTC_OK) return st;
-      const void* X2 = (const char*)X + (size_t)64 * d.in * 2;
-      void* Y2 = (char*)Y + (size_t)64 * d.out * ysz;
-      if (rest >= 17) return gemm_rows(q, d, packed, codebook, alpha, mu, X2, is_bf16, rest, Y2, (int)y_dtype, workspace);
-      return gemv_mfma(q, d, packed, codebook, alpha, mu, X2, is_bf16, rest, Y2, (int)y_dtype, workspace);
-    }
-  }
   // Few activation rows: decoding dominates, and the decode engine of btc_gemv (table entries
   // that are matrix-core operands, 16 rows per pass) is several times quicker than a 256-row tile
   // that is mostly empty.  Up to 64 rows are served in blocks of 16.
   if (M <= 64 && gemv_mfma_covers(d, M < 16 ? M : 16) &&
-      ((M + 15) / 16) * gemv_mfma_estimate_us(d, M < 16 ? M : 16) <
-          (gemm_tiled_covers(d, M) ? gemm_tiled_estimate_us(d, M) : 1e30)) {
+      ((M + 15) / 16) * gemv_mfma_estimate_us(d, M < 16 ? M : 16) < decode_us) {
     const size_t xsz = 2, ysz = y_dtype == BTC_F32 ? 4 : 2;
     for (int m0 = 0; m0 < M; m0 += 16) {
       const int rows = M - m0 < 16 ? M - m0 : 16;
@@ -111,12 +98,13 @@ btc_status btc_gemm(void* stream, const btc_shape* s, const uint32_t* packed, co
     }
     return BTC_OK;
   }
-  // many rows and enough output tiles to fill the chip: expand the signs once, stream both operands (if the caller's workspace holds the bytes)
-  if (gemm_wide_covers(d, M) && workspace && workspace_bytes >= gemm_wide_workspace_bytes(d, M))
+  // everything else on chunk lengths 9 and 10: the weights decoded inside the contraction
+  if (gemm_decode_covers(d, M))
+    return gemm_decode(q, d, packed, codebook, alpha, mu, X, is_bf16, M, Y, (int)y_dtype, workspace, workspace_bytes,
+                       /*clear_workspace=*/0);
+  // other settings with many rows and enough output tiles to fill the chip: the signs expanded once per call
+  if (gemm_wide_covers(d, M))
     return gemm_wide(q, d, packed, codebook, alpha, mu, X, is_bf16, M, Y, (int)y_dtype, workspace, workspace_bytes);
-  if (gemm_tiled_covers(d, M))   // adds the activation rows up itself
-    return gemm_tiled(q, d, packed, codebook, alpha, mu, X, is_bf16, M, Y, (int)y_dtype, workspace, workspace_bytes,
-                      /*clear_workspace=*/0);
   rowsum_kernel<<<(M + 3) / 4, 256, 0, q>>>((const uint16_t*)X, M, d.in, is_bf16, rowsum);
   return gemm_generic(q, d, packed, codebook, alpha, mu, X, is_bf16, M, Y, (int)y_dtype, rowsum);
 }

@@ -1,5 +1,5 @@
 // Generic prefill product  Y[M][out] = X[M][in] . W_hat^T  on the matrix cores: any chunk length,
-// any index width, ragged shapes.  The tuned kernel (btc_gemm_tiled.hip) covers the common settings.
+// any index width, ragged shapes.  The tuned kernel (btc_gemm_decode.hip) covers the common settings.
 //
 // At many activation rows the layer is a dense contraction, so instead of
 // the lookup-and-accumulate scheme of appendix "Binary Codebook LUT-GEMM" the

@@ -1,13 +1,12 @@
-// Prefill product for many activation rows (512 or more, and enough output tiles to fill the chip):  Y[M][out] = X[M][in] . W_hat^T, in two kernels.
+// Prefill product for many activation rows (512 or more, and enough output tiles to fill the chip) on the settings that
+// btc_gemm_decode.hip has no tables for (chunk lengths other than 9 and 10, more than 10 index bits):
+// Y[M][out] = X[M][in] . W_hat^T, in two kernels.
 //
-// At this size every weight tile is needed by M / 256 workgroups, so decoding it inside each of them
-// (btc_gemm_tiled.hip) repeats the table look-ups M / 256 times, and those look-ups and the tile
-// writes take more LDS time than the matrix cores leave.  Here the sign matrix B_hat of the layer
-// (Algorithm "Binary Transformation and Compression": W_hat = alpha * B_hat + mu) is expanded once
-// per call into a scratch matrix of one byte per weight -- the HIGH byte of +-1.0 in the operand's
-// 16-bit format -- and the contraction kernel streams tiles of it, like tiles of X, straight from
-// memory into LDS with the load-to-LDS instructions (no registers, no LDS writes by a wave, nothing
-// to decode).  alpha and mu are applied afterwards in fp32.
+// At this size every weight tile is needed by M / 256 workgroups.  The sign matrix B_hat of the layer (Algorithm "Binary
+// Transformation and Compression": W_hat = alpha * B_hat + mu) is expanded once per call into a scratch matrix of one
+// byte per weight -- the HIGH byte of +-1.0 in the operand's 16-bit format -- and the contraction kernel streams tiles
+// of it, like tiles of X, straight from memory into LDS with the load-to-LDS instructions (no registers, no LDS writes
+// by a wave, nothing to decode).  alpha and mu are applied afterwards in fp32.
 //
 // Contraction kernel, per workgroup (256 activation rows x BN = 32 NF weight rows, k-tiles of 80):
 //   * 4 contraction waves, 64 activation rows each, 2 x NF accumulators of MFMA 32x32x16; both
@@ -110,8 +109,6 @@ __device__ __forceinline__ void load_to_lds_16(const __amdgpu_buffer_rsrc_t& rsr
 #endif
 }
 
-constexpr int kRowsAtOnce = 4;      // rows of index words a block of the first kernel holds in LDS
-constexpr int kRowWords = 1024;     // words per such row at most (longer rows: read from memory)
 
 // ---- first kernel: the sign matrix as bytes, WB[out][pitch] (pitch = 80 * number of k-tiles; the
 // columns past `in` hold the rest of the last chunk's pattern, then zeros: they only ever meet
@@ -153,87 +150,6 @@ __global__ __launch_bounds__(256) void expand_signs_kernel(Dims d, const uint32_
   const int pieces = pitch >> 4;
   const uint32_t id = (blockIdx.x - (uint32_t)sum_blocks) * 256u + threadIdx.x;       // out * pitch < 2^31
   const uint32_t mask = (1u << d.b) - 1u;
-  if (d.v == 10 && d.b <= 10 && d.wpr <= kRowWords) {
-    // Chunk length 10: the 16 columns of a piece lie inside three consecutive chunks.  Their
-    // (inverted) patterns, from a table in LDS, are strung together, shifted to the piece's first
-    // column, and every 4 bits are spread over the 4 bytes of a word by one 24-bit multiply.
-    // A block takes kRowsAtOnce rows at a time: their index words are fetched once, coalesced, into
-    // LDS, and the threads pick their three index fields from there (as loads from memory the
-    // six words per thread cost more than everything else in this kernel).
-    __shared__ uint32_t npat[1024];
-    __shared__ uint32_t words[kRowsAtOnce * kRowWords + 1];
-    for (int k = threadIdx.x; k < (1 << d.b); k += 256) npat[k] = ~codebook[k] & 0x3FFu;
-    const int groups = (d.out + kRowsAtOnce - 1) / kRowsAtOnce;
-    for (int grp = (int)blockIdx.x - sum_blocks; grp < groups; grp += expand_blocks) {
-      const int row0 = grp * kRowsAtOnce, rows = min(kRowsAtOnce, d.out - row0);
-      __syncthreads();                                     // the previous group's words are no longer read
-      for (int i = threadIdx.x; i < rows * d.wpr; i += 256) words[i] = packed[(size_t)row0 * d.wpr + i];
-      __syncthreads();
-      int r = 0, pc = threadIdx.x;
-      while (pc >= pieces) { pc -= pieces; ++r; }
-      while (r < rows) {
-        const uint32_t* prow = words + r * d.wpr;
-        const int j0 = (pc * 16) / 10, t0 = pc * 16 - 10 * j0;
-        uint32_t bits = 0u;
-#pragma unroll
-        for (int u = 0; u < 3; ++u) {
-          const int j = j0 + u;
-          if (j < d.nchunks) {                             // (past the last chunk: +1 bytes, they meet zero activations)
-            const uint32_t bit = (uint32_t)j * (uint32_t)d.b;
-            const uint32_t w0 = bit >> 5, sh = bit & 31u;
-            const uint32_t lo = prow[w0];
-            const uint32_t hi = prow[w0 + 1];              // (one word past the row at most: inside `words`, shifted out)
-            bits |= npat[__builtin_amdgcn_alignbit(hi, lo, sh) & mask] << (10 * u);
-          }
-        }
-        const uint32_t n16 = bits >> t0;
-        uint32_t w[4];
-#pragma unroll
-        for (int q = 0; q < 4; ++q)
-          w[q] = (((__umul24((n16 >> (4 * q)) & 0xFu, 0x204081u)) & 0x01010101u) << 7) | (hi_byte * 0x01010101u);
-        *(uint4*)(WB + (size_t)(row0 + r) * pitch + (size_t)pc * 16) = make_uint4(w[0], w[1], w[2], w[3]);
-        pc += 256;
-        while (pc >= pieces) { pc -= pieces; ++r; }
-      }
-    }
-    return;
-  }
-  if (d.v == 10 && d.b <= 10) {
-    // The same for rows too long for the LDS copy: index words straight from memory.
-    __shared__ uint32_t npat[1024];
-    for (int k = threadIdx.x; k < (1 << d.b); k += 256) npat[k] = ~codebook[k] & 0x3FFu;
-    __syncthreads();
-    const uint32_t total = (uint32_t)d.out * (uint32_t)pieces;
-    for (uint32_t it = id; it < total; it += (uint32_t)expand_blocks * 256u) {
-    const int row = (int)(it / (uint32_t)pieces), pc = (int)(it - (uint32_t)row * (uint32_t)pieces);
-    const uint32_t* prow = packed + (size_t)row * d.wpr;
-    const int j0 = (pc * 16) / 10, t0 = pc * 16 - 10 * j0;
-    uint32_t idx[3];
-#pragma unroll
-    for (int u = 0; u < 3; ++u) {
-      const int j = j0 + u;
-      idx[u] = 0xFFFFFFFFu;
-      if (j < d.nchunks) {                               // (past the last chunk: +1 bytes, they meet zero activations)
-        const uint32_t bit = (uint32_t)j * (uint32_t)d.b;
-        const uint32_t w0 = bit >> 5, sh = bit & 31u;
-        const uint32_t lo = prow[w0];
-        const uint32_t hi = (sh + d.b > 32u) ? prow[w0 + 1] : 0u;   // inside the row whenever the field crosses
-        idx[u] = __builtin_amdgcn_alignbit(hi, lo, sh) & mask;
-      }
-    }
-    uint32_t bits = 0u;
-#pragma unroll
-    for (int u = 0; u < 3; ++u)
-      if (idx[u] != 0xFFFFFFFFu) bits |= npat[idx[u]] << (10 * u);
-    const uint32_t n16 = bits >> t0;
-    uint32_t w[4];
-#pragma unroll
-    for (int q = 0; q < 4; ++q)
-      w[q] = (((__umul24((n16 >> (4 * q)) & 0xFu, 0x204081u)) & 0x01010101u) << 7) | (hi_byte * 0x01010101u);
-    *(uint4*)(WB + (size_t)row * pitch + (size_t)pc * 16) = make_uint4(w[0], w[1], w[2], w[3]);
-    }
-    return;
-  }
   for (uint32_t it = id; it < (uint32_t)d.out * (uint32_t)pieces; it += (uint32_t)expand_blocks * 256u) {
   const int row = (int)(it / (uint32_t)pieces), pc = (int)(it - (uint32_t)row * (uint32_t)pieces);
   const uint32_t* prow = packed + (size_t)row * d.wpr;
@@ -660,8 +576,8 @@ extern "C" int btc_debug_wide_stamps(unsigned long long* host, int n) {
 #endif
 
 bool gemm_wide_covers(const Dims& d, int M) {
-  // worth its first kernel only when the 256 x 160 output tiles fill the chip (below that the tiled
-  // kernel, which can split a call along k, is as fast or faster)
+  if (gemm_decode_covers(d, M)) return false;                 // (decodes inside the contraction: faster)
+  // worth its first kernel only when the 256 x 160 output tiles fill the chip
   if (M < 512 || d.b > 16) return false;
   if ((long long)((M + wide::kBM - 1) / wide::kBM) * ((d.out + 159) / 160) < 224) return false;
   if (d.in % 16 != 0) return false;                           // 16-byte pieces of an activation row
@@ -686,8 +602,6 @@ btc_status gemm_wide(hipStream_t q, const Dims& d, const uint32_t* packed, const
   // a few thousand blocks that each walk over the pieces (the table in LDS is filled once per block)
   int expand_blocks = (int)std::min<long long>((pieces + 255) / 256, 2048);
   const int sum_blocks = (M + 3) / 4;
-  if (d.v == 10 && d.b <= 10 && d.wpr <= kRowWords)      // blocks walk over groups of kRowsAtOnce rows
-    expand_blocks = std::min((d.out + kRowsAtOnce - 1) / kRowsAtOnce, 2048);
   if (is_bf16)
     expand_signs_kernel<true><<<expand_blocks + sum_blocks, 256, 0, q>>>(d, packed, codebook, WB, pitch, expand_blocks,
                                                                          (const uint16_t*)X, M, rs);

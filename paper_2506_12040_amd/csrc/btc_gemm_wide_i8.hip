@@ -65,8 +65,6 @@ __device__ __forceinline__ void load_to_lds_16(const __amdgpu_buffer_rsrc_t& rsr
 // of k-tiles; zero past column `in`), one thread per 16 bytes
 // at a time; the first blocks of the grid (all but `expand_blocks`) add up the codes of the activation
 // rows instead, one wave per row (exact integers).
-constexpr int kRowsAtOnce = 4;      // rows of index words a block of the first kernel holds in LDS
-constexpr int kRowWords = 1024;     // words per such row at most (longer rows: read from memory)
 
 __global__ __launch_bounds__(256) void expand_signs_i8_kernel(Dims d, const uint32_t* __restrict__ packed,
                                                               const uint32_t* __restrict__ codebook,
@@ -102,89 +100,6 @@ __global__ __launch_bounds__(256) void expand_signs_i8_kernel(Dims d, const uint
   const int pieces = pitch >> 4;
   const uint32_t id = (blockIdx.x - (uint32_t)sum_blocks) * 256u + threadIdx.x;       // out * pitch < 2^31
   const uint32_t mask = (1u << d.b) - 1u;
-  if (d.v == 10 && d.b <= 10 && d.wpr <= kRowWords) {
-    // Chunk length 10: the 16 columns of a piece lie inside three consecutive chunks.  Their
-    // (inverted) patterns, from a table in LDS, are strung together, shifted to the piece's first
-    // column, and every 4 bits are spread over the 4 bytes of a word by one 24-bit multiply.
-    // A block takes kRowsAtOnce rows at a time: their index words are fetched once, coalesced, into
-    // LDS, and the threads pick their three index fields from there.
-    __shared__ uint32_t npat[1024];
-    __shared__ uint32_t words[kRowsAtOnce * kRowWords + 1];
-    for (int k = threadIdx.x; k < (1 << d.b); k += 256) npat[k] = ~codebook[k] & 0x3FFu;
-    const int groups = (d.out + kRowsAtOnce - 1) / kRowsAtOnce;
-    for (int grp = (int)blockIdx.x - sum_blocks; grp < groups; grp += expand_blocks) {
-      const int row0 = grp * kRowsAtOnce, rows = min(kRowsAtOnce, d.out - row0);
-      __syncthreads();                                     // the previous group's words are no longer read
-      for (int i = threadIdx.x; i < rows * d.wpr; i += 256) words[i] = packed[(size_t)row0 * d.wpr + i];
-      __syncthreads();
-      int r = 0, pc = threadIdx.x;
-      while (pc >= pieces) { pc -= pieces; ++r; }
-      while (r < rows) {
-        uint4 o = make_uint4(0u, 0u, 0u, 0u);
-        if (pc * 16 < d.in) {                              // (`in` is a multiple of 16: a piece is wholly inside or outside)
-          const uint32_t* prow = words + r * d.wpr;
-          const int j0 = (pc * 16) / 10, t0 = pc * 16 - 10 * j0;
-          uint32_t bits = 0u;
-#pragma unroll
-          for (int u = 0; u < 3; ++u) {
-            const int j = j0 + u;
-            if (j < d.nchunks) {
-              const uint32_t bit = (uint32_t)j * (uint32_t)d.b;
-              const uint32_t w0 = bit >> 5, sh = bit & 31u;
-              const uint32_t lo = prow[w0];
-              const uint32_t hi = prow[w0 + 1];            // (one word past the row at most: inside `words`, shifted out)
-              bits |= npat[__builtin_amdgcn_alignbit(hi, lo, sh) & mask] << (10 * u);
-            }
-          }
-          const uint32_t n16 = bits >> t0;
-          uint32_t w[4];
-#pragma unroll
-          for (int q = 0; q < 4; ++q)   // +1 = 0x01, -1 = 0xFF = 0x01 ^ 0xFE
-            w[q] = 0x01010101u ^ (((__umul24((n16 >> (4 * q)) & 0xFu, 0x204081u)) & 0x01010101u) * 0xFEu);
-          o = make_uint4(w[0], w[1], w[2], w[3]);
-        }
-        *(uint4*)(WB + (size_t)(row0 + r) * pitch + (size_t)pc * 16) = o;
-        pc += 256;
-        while (pc >= pieces) { pc -= pieces; ++r; }
-      }
-    }
-    return;
-  }
-  if (d.v == 10 && d.b <= 10) {
-    // The same for rows too long for the LDS copy: index words straight from memory.
-    __shared__ uint32_t npat[1024];
-    for (int k = threadIdx.x; k < (1 << d.b); k += 256) npat[k] = ~codebook[k] & 0x3FFu;
-    __syncthreads();
-    const uint32_t total = (uint32_t)d.out * (uint32_t)pieces;
-    for (uint32_t it = id; it < total; it += (uint32_t)expand_blocks * 256u) {
-      const int row = (int)(it / (uint32_t)pieces), pc = (int)(it - (uint32_t)row * (uint32_t)pieces);
-      uint4 o = make_uint4(0u, 0u, 0u, 0u);
-      if (pc * 16 < d.in) {                              // (`in` is a multiple of 16: a piece is wholly inside or outside)
-        const uint32_t* prow = packed + (size_t)row * d.wpr;
-        const int j0 = (pc * 16) / 10, t0 = pc * 16 - 10 * j0;
-        uint32_t bits = 0u;
-#pragma unroll
-        for (int u = 0; u < 3; ++u) {
-          const int j = j0 + u;
-          if (j < d.nchunks) {
-            const uint32_t bit = (uint32_t)j * (uint32_t)d.b;
-            const uint32_t w0 = bit >> 5, sh = bit & 31u;
-            const uint32_t lo = prow[w0];
-            const uint32_t hi = (sh + d.b > 32u) ? prow[w0 + 1] : 0u;   // inside the row whenever the field crosses
-            bits |= npat[__builtin_amdgcn_alignbit(hi, lo, sh) & mask] << (10 * u);
-          }
-        }
-        const uint32_t n16 = bits >> t0;
-        uint32_t w[4];
-#pragma unroll
-        for (int q = 0; q < 4; ++q)   // +1 = 0x01, -1 = 0xFF = 0x01 ^ 0xFE
-          w[q] = 0x01010101u ^ (((__umul24((n16 >> (4 * q)) & 0xFu, 0x204081u)) & 0x01010101u) * 0xFEu);
-        o = make_uint4(w[0], w[1], w[2], w[3]);
-      }
-      *(uint4*)(WB + (size_t)row * pitch + (size_t)pc * 16) = o;
-    }
-    return;
-  }
   for (uint32_t it = id; it < (uint32_t)d.out * (uint32_t)pieces; it += (uint32_t)expand_blocks * 256u) {
     const int row = (int)(it / (uint32_t)pieces), pc = (int)(it - (uint32_t)row * (uint32_t)pieces);
     const uint32_t* prow = packed + (size_t)row * d.wpr;
@@ -548,6 +463,7 @@ static size_t sign_bytes(const Dims& d) { return ((size_t)d.out * pitch_of(d) + 
 }  // namespace wide8
 
 bool gemm_wide_i8_covers(const Dims& d, int M) {
+  if (gemm_decode_i8_covers(d, M)) return false;              // (decodes inside the contraction)
   // worth its first kernel only when the 256 x 160 output tiles fill the chip
   if (M < 512 || d.b > 16) return false;
   if ((long long)((M + wide8::kBM - 1) / wide8::kBM) * ((d.out + 159) / 160) < 224) return false;
@@ -573,8 +489,6 @@ btc_status gemm_wide_i8(hipStream_t q, const Dims& d, const uint32_t* packed, co
   // a few thousand blocks that each walk over the pieces
   int expand_blocks = (int)std::min<long long>((pieces + 255) / 256, 2048);
   const int sum_blocks = (M + 3) / 4;
-  if (d.v == 10 && d.b <= 10 && d.wpr <= kRowWords)      // blocks walk over groups of kRowsAtOnce rows
-    expand_blocks = std::min((d.out + kRowsAtOnce - 1) / kRowsAtOnce, 2048);
   expand_signs_i8_kernel<<<expand_blocks + sum_blocks, 256, 0, q>>>(d, packed, codebook, WB, pitch, expand_blocks, Q, M, qs);
   btc_status st = launch_status();
   if (st != BTC_OK) return st;

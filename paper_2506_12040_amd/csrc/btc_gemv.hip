@@ -5,7 +5,7 @@
 
 // Rough duration in microseconds of one decode pass over the matrix for a single activation
 // row (a fixed chain of round trips plus streaming time; fitted to measurements on 7B-shaped
-// layers).  Compared with the tiled contraction kernel's own estimate to decide whether a
+// layers).  Compared with the decoding contraction kernel's own estimate to decide whether a
 // batch is served by one pass per row or by one pass of that kernel for all rows.
 static double row_pass_us(const btc::Dims& d) { return 3.5 + 1.8e-6 * (double)d.out * d.wpr * 4; }
 
@@ -42,7 +42,7 @@ static int choose_engine(const Dims& d, int batch) {
       // when the matrix is large and so wide that the table engine cannot use its streaming kernel, and for
       // every large matrix with 10-bit indices (128 KB table: one workgroup per compute unit only).
       engine = BTC_ENGINE_MFMA;
-    else if (batch > 1 && gemm_tiled_covers(d, batch) && batch * row_pass_us(d) > gemm_tiled_estimate_us(d, batch))
+    else if (batch > 1 && gemm_decode_covers(d, batch) && batch * row_pass_us(d) > gemm_decode_estimate_us(d, batch))
       engine = BTC_ENGINE_TILED;
     else if ((bytes < (3LL << 20) || !lut_engine_covers(d)) && expand_engine_covers(d))
       // Small matrices are bound by the chain of memory round trips: the register-resident engine has the
@@ -64,6 +64,13 @@ static int choose_engine(const Dims& d, int batch) {
 // Whether an engine parks anything in the caller's workspace.
 static bool engine_uses_workspace(int engine) {
   return engine == BTC_ENGINE_LUT || engine == BTC_ENGINE_MFMA || engine == BTC_ENGINE_TILED;
+}
+
+// How much of it.
+static size_t engine_workspace_bytes(const Dims& d, int engine, int batch) {
+  const size_t behind = engine == BTC_ENGINE_MFMA ? gemv_mfma_workspace_bytes(d, batch)
+                        : engine == BTC_ENGINE_TILED ? gemm_decode_workspace_bytes(d, batch) : 0;
+  return gemv_table_region_bytes(d) + behind;
 }
 
 // Whether btc_gemv on this shape and batch parks anything in (and expects zeros in) its workspace.
@@ -106,15 +113,13 @@ static btc_status gemv_dispatch(int engine, void* stream, const btc_shape* s, co
       // each index is decoded once for the whole batch.  A k-split call parks partial sums in the workspace
       // (after the table engine's slots of this shape) and zeroes them again in its second pass, so that
       // one zero-filled workspace serves any sequence of calls, whatever their shapes and batch sizes.
-      if (!gemm_tiled_covers(d, batch)) return BTC_ERR_UNSUPPORTED;
+      if (!gemm_decode_covers(d, batch)) return BTC_ERR_UNSUPPORTED;
       const size_t off = gemv_table_region_bytes(d);
-      const size_t need = gemm_tiled_workspace_bytes(d, batch);
-      if (need > 0) {
-        if (!workspace || workspace_bytes < off + need) return BTC_ERR_WORKSPACE;
-        if (!aligned16(workspace)) return BTC_ERR_ALIGN;
-      }
-      return gemm_tiled(q, d, packed, codebook, alpha, mu, x, /*is_bf16=*/0, batch, y, (int)y_dtype,
-                        need > 0 ? (char*)workspace + off : nullptr, need, /*clear_workspace=*/1);
+      const size_t need = gemm_decode_workspace_bytes(d, batch);
+      if (!workspace || workspace_bytes < off + need) return BTC_ERR_WORKSPACE;
+      if (!aligned16(workspace)) return BTC_ERR_ALIGN;
+      return gemm_decode(q, d, packed, codebook, alpha, mu, x, /*is_bf16=*/0, batch, y, (int)y_dtype,
+                         (char*)workspace + off, need, /*clear_workspace=*/1);
     }
     case BTC_ENGINE_EXPAND:
     case BTC_ENGINE_FP4:
@@ -129,7 +134,7 @@ static btc_status gemv_dispatch(int engine, void* stream, const btc_shape* s, co
       return BTC_OK;
     case BTC_ENGINE_LUT:
       if (!lut_engine_covers(d)) return BTC_ERR_UNSUPPORTED;
-      if (!workspace || workspace_bytes < btc_workspace_bytes(s, batch, 0)) return BTC_ERR_WORKSPACE;
+      if (!workspace || workspace_bytes < gemv_table_region_bytes(d)) return BTC_ERR_WORKSPACE;
       if (!aligned16(workspace)) return BTC_ERR_ALIGN;
       // One pass of the table engine per activation row; the passes share the
       // workspace, which is safe because they are ordered on the stream.
@@ -195,7 +200,7 @@ btc_status btc_gemv_static(void* stream, const btc_shape* s, const uint32_t* pac
   const int engine = choose_engine(d, batch);
   if (!engine_uses_workspace(engine))   // most single-row calls: nothing is parked anywhere
     return gemv_dispatch(engine, stream, s, packed, codebook, alpha, mu, x, batch, y, y_dtype, nullptr, 0);
-  const size_t need = btc_workspace_bytes(s, batch, 0);
+  const size_t need = engine_workspace_bytes(d, engine, batch);
   if (need > kStaticScratchBytes) return BTC_ERR_WORKSPACE;   // larger than the static array: use btc_gemv
   void* ws = nullptr;
   st = static_scratch(&ws);

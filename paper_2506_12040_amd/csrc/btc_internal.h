@@ -95,12 +95,19 @@ size_t gemm_wide_i8_workspace_bytes(const Dims& d, int M);
 btc_status gemm_wide_i8(hipStream_t q, const Dims& d, const uint32_t* packed, const uint32_t* codebook,
                         const float* alpha, const float* mu, const float* wsum, const uint8_t* Q, const float* lo,
                         const float* step, int M, void* Y, int y_dtype, void* workspace, size_t workspace_bytes);
-// Prefill kernels: the tuned tiling (btc_gemm_tiled.hip) and the generic one (btc_gemm_generic.hip).
-bool gemm_tiled_covers(const Dims& d, int M);
-btc_status gemm_tiled(hipStream_t q, const Dims& d, const uint32_t* packed, const uint32_t* codebook,
-                      const float* alpha, const float* mu, const void* X, int is_bf16, int M, void* Y, int y_dtype,
-                      void* workspace, size_t workspace_bytes, int clear_workspace);
-size_t gemm_tiled_workspace_bytes(const Dims& d, int M);   // 0 unless the call is split along k
+// Prefill kernels: weights decoded inside the contraction (btc_gemm_decode.hip; chunk lengths 9 and 10), on 16-bit
+// activations and on 8-bit codes, and the generic one (btc_gemm_generic.hip).
+bool gemm_decode_covers(const Dims& d, int M);
+bool gemm_decode_i8_covers(const Dims& d, int M);
+btc_status gemm_decode(hipStream_t q, const Dims& d, const uint32_t* packed, const uint32_t* codebook,
+                       const float* alpha, const float* mu, const void* X, int is_bf16, int M, void* Y, int y_dtype,
+                       void* workspace, size_t workspace_bytes, int clear_workspace);
+btc_status gemm_decode_i8(hipStream_t q, const Dims& d, const uint32_t* packed, const uint32_t* codebook,
+                          const float* alpha, const float* mu, const float* wsum, const uint8_t* Q, const float* lo,
+                          const float* step, int M, void* Y, int y_dtype, void* workspace, size_t workspace_bytes);
+size_t gemm_decode_workspace_bytes(const Dims& d, int M);   // 0 unless the call is split along k
+size_t gemm_decode_i8_workspace_bytes(const Dims& d, int M);
+double gemm_decode_estimate_us(const Dims& d, int M);       // rough duration, for engine selection
 // many activation rows (btc_gemm_wide.hip): the signs expanded once per call into a byte matrix in the workspace,
 // contracted by a kernel that streams both operands into LDS with load-to-LDS instructions
 bool gemm_wide_covers(const Dims& d, int M);
@@ -108,7 +115,6 @@ size_t gemm_wide_workspace_bytes(const Dims& d, int M);
 btc_status gemm_wide(hipStream_t q, const Dims& d, const uint32_t* packed, const uint32_t* codebook,
                      const float* alpha, const float* mu, const void* X, int is_bf16, int M, void* Y, int y_dtype,
                      void* workspace, size_t workspace_bytes);
-double gemm_tiled_estimate_us(const Dims& d, int M);       // rough duration, for engine selection
 // Leading part of a btc_gemv workspace that must stay zero between calls (the table engine's slots).
 size_t gemv_table_region_bytes(const Dims& d);
 btc_status gemm_generic(hipStream_t q, const Dims& d, const uint32_t* packed, const uint32_t* codebook,

@@ -243,11 +243,6 @@ btc_status btc_gemm_aq(void* stream, const btc_shape* s, const uint32_t* packed,
   hipStream_t q = (hipStream_t)stream;
   {
     const Dims d = dims_of(*s);
-#ifdef BTC_PLAN_ENV
-    if (const char* e = getenv("BTC_ROUTE")) {
-      if (e[0] == 'w') return gemm_wide_i8(q, d, packed, codebook, alpha, mu, wsum, Q, lo, step, M, Y, (int)y_dtype, workspace, workspace_bytes);
-    }
-#endif
     if (M > 16 && gemm_decode_i8_covers(d, M))
       return gemm_decode_i8(q, d, packed, codebook, alpha, mu, wsum, Q, lo, step, M, Y, (int)y_dtype, workspace,
                             workspace_bytes);

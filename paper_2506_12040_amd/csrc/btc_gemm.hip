@@ -73,12 +73,6 @@ btc_status btc_gemm(void* stream, const btc_shape* s, const uint32_t* packed, co
   const Dims d = dims_of(*s);
   float* rowsum = (float*)((char*)workspace + 16);
   const int is_bf16 = x_dtype == BTC_BF16;
-#ifdef BTC_PLAN_ENV
-  if (const char* e = getenv("BTC_ROUTE")) {
-    if (e[0] == 'd') return gemm_decode(q, d, packed, codebook, alpha, mu, X, is_bf16, M, Y, (int)y_dtype, workspace, workspace_bytes, 0);
-    if (e[0] == 'w') return gemm_wide(q, d, packed, codebook, alpha, mu, X, is_bf16, M, Y, (int)y_dtype, workspace, workspace_bytes);
-  }
-#endif
   const double decode_us = gemm_decode_covers(d, M) ? gemm_decode_estimate_us(d, M) : 1e30;
   // 17..64 activation rows: the same operand scheme with two or four blocks of activation rows
   // per table read, one pass over the index stream.

@@ -29,9 +29,9 @@
 // What bounds it: at 256 busy compute units the clock and the traffic into LDS as much as the matrix pipe (5120 x 5120 at
 // M = 2048: 88 us = 1215 TFLOP/s; without the decoders 70 us, with half the activation loads 73 us -- timing-only
 // builds), on few activation rows prologue, epilogue and the second pass.  Against the kernels it took over from:
-// 13824 x 5120 at M = 2048 237 us (251: signs expanded to memory first), 5120 x 13824 at M = 512 78 us (106: a table of
-// expanded codewords, activations through registers), v = 9 at M = 203 21 / 36 / 36 us on the 7B shapes (the generic
-// kernel: 230 / 600 / 640), codes at M = 1024 47 / 95 / 89 us on the 13B shapes (16-bit copies of the codes: 90 .. 190).
+// 13824 x 5120 at M = 2048 237 us (251 with the signs expanded to memory first), at M = 512 69 us (85 with a table of
+// expanded codewords and activations through registers); the seven products of a 7B-shaped layer at v = 9, M = 203
+// 212 us (generic kernel: 2510); of a 13B-shaped layer on codes at M = 1024 541 us (825 as 16-bit copies of the codes).
 #include <hip/hip_bf16.h>
 #include <hip/hip_fp16.h>
 
@@ -821,17 +821,6 @@ static Plan make_plan(const Dims& d, int M, int op) {
         if (cost < best.est_us) best = Plan{ma, nf, sp, tps, cost};
       }
     }
-#ifdef BTC_PLAN_ENV
-  if (const char* e = getenv("BTC_PLAN")) {
-    int a, n, s;
-    if (sscanf(e, "%d,%d,%d", &a, &n, &s) == 3 && a > 0) {
-      s = std::min(s, ntiles);
-      int tps = (ntiles + s - 1) / s;
-      s = (ntiles + tps - 1) / tps;
-      best = Plan{a, n, s, tps, 1.0};
-    }
-  }
-#endif
   return best;
 }
 

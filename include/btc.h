@@ -15,6 +15,8 @@
  *   - Every array pointer is a DEVICE pointer owned by the caller unless the
  *     comment says "host".  The library allocates no device memory and keeps
  *     no state between calls; scratch space is the caller's `workspace`.
+ *     (btc_pack and btc_update hold 64 bytes of pinned host memory per calling
+ *     thread, until the thread ends, for the result of their range check.)
  *   - `stream` is a hipStream_t passed as void* (NULL = the default stream).
  *     Compute calls enqueue work and return; only btc_pack and btc_update
  *     wait, to return the result of a range check (see there).
@@ -102,7 +104,7 @@ size_t btc_workspace_bytes(const btc_shape* s, int32_t rows, int is_gemm);
  *   packed : uint32 [out][words_per_row]; index j of row i occupies bits
  *            [j*b, (j+1)*b) of row i's stream, bit p of the stream being bit
  *            (p & 31) of word (p >> 5); unused tail bits are written as 0.
- *   workspace : >= 16 bytes, receives a range-check flag.
+ *   workspace : >= 16 bytes (scratch).
  * Waits for the stream: returns BTC_ERR_INDEX_RANGE if any index is outside
  * [0, K) (packed is then unspecified). */
 btc_status btc_pack(void* stream, const btc_shape* s, const int32_t* idx, uint32_t* packed,

@@ -22,6 +22,23 @@ btc_status check_shape(const btc_shape* s) {
   return BTC_OK;
 }
 
+uint32_t* host_word() {
+  struct Word {
+    uint32_t* p = nullptr;
+    ~Word() {
+      if (p) (void)hipHostFree(p);
+    }
+  };
+  static thread_local Word word;         // the call waits before it returns: one word per thread is enough
+  if (!word.p) {
+    void* p = nullptr;
+    if (hipHostMalloc(&p, 64, hipHostMallocPortable | hipHostMallocMapped) != hipSuccess) return nullptr;
+    word.p = (uint32_t*)p;
+  }
+  *(volatile uint32_t*)word.p = 0u;
+  return word.p;
+}
+
 }  // namespace btc
 
 extern "C" {

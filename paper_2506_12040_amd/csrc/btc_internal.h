@@ -121,6 +121,11 @@ btc_status gemm_generic(hipStream_t q, const Dims& d, const uint32_t* packed, co
                         const float* alpha, const float* mu, const void* X, int is_bf16, int M, void* Y,
                         int y_dtype, const float* rowsum);
 
+// A word of pinned host memory for the calling thread, set to zero: where the calls that wait (btc_pack, btc_update) have
+// their kernels report an index out of range (reading a word of device memory back costs a staged copy and a second
+// trip).  Null if it cannot be had.
+uint32_t* host_word();
+
 inline btc_status launch_status() {
   return hipGetLastError() == hipSuccess ? BTC_OK : BTC_ERR_HIP;
 }

@@ -1,7 +1,8 @@
-"""Thin ctypes binding of libbtc_hip.so: same names as include/btc.h, argument
-marshalling only.  Tensors are torch CUDA(HIP) tensors used purely as device
-buffers; every step of the computation runs in the library's kernels.  There
-is no CPU fallback: a missing library raises.
+"""Thin binding of libbtc_hip.so: same names as include/btc.h, argument
+marshalling only (in C for the calls that launch work: csrc/btc_python.c; by
+ctypes for the host-only ones).  Tensors are torch CUDA(HIP) tensors used purely
+as device buffers; every step of the computation runs in the library's kernels.
+There is no CPU fallback: a missing library raises.
 """
 from __future__ import annotations
 
@@ -101,30 +102,52 @@ def lib() -> ctypes.CDLL:
     return _lib
 
 
+class _Entry:
+    """An entry point that launches work: called with Python objects in the order of its C parameters behind the stream."""
+    __slots__ = ("name", "address")
+    native = None      # _native.call
+
+    def __init__(self, name: str):
+        self.name, self.address = name, 0
+
+    def __call__(self, stream, *args) -> None:
+        if not self.address:
+            self._load()
+        status = _Entry.native(self.address, _current_stream() if stream is None else stream if isinstance(stream, int)
+                               else stream.cuda_stream, *args)
+        if status != BTC_OK:
+            raise BtcError(status, self.name)
+
+    def _load(self) -> None:
+        if _Entry.native is None:
+            try:
+                from ._native import call
+            except ImportError as e:
+                raise RuntimeError("the package's extension module _native is missing: run "
+                                   "paper_2506_12040_amd.build.build() (there is no fallback path)") from e
+            _Entry.native = call
+        self.address = ctypes.cast(getattr(lib(), self.name), ctypes.c_void_p).value
+
+
+_raw_stream = _device = None
+
+
+def _current_stream() -> int:
+    """The address of torch's current stream on the current device."""
+    global _raw_stream, _device
+    if _raw_stream is None:
+        import torch
+        torch.cuda.current_stream()      # (initialises torch's side once)
+        _raw_stream, _device = torch._C._cuda_getCurrentRawStream, torch._C._cuda_getDevice
+    return _raw_stream(_device())
+
+
 def status_str(status: int) -> str:
     return lib().btc_status_str(int(status)).decode()
 
 
-def _ptr(t) -> ctypes.c_void_p:
-    """Device (or host) address of a torch tensor, a raw int address, or None."""
-    if t is None:
-        return ctypes.c_void_p(0)
-    if isinstance(t, int):
-        return ctypes.c_void_p(t)
-    return ctypes.c_void_p(t.data_ptr())
-
-
-def _stream(stream) -> ctypes.c_void_p:
-    if stream is None:
-        import torch
-        return ctypes.c_void_p(torch.cuda.current_stream().cuda_stream)
-    if isinstance(stream, int):
-        return ctypes.c_void_p(stream)
-    return ctypes.c_void_p(stream.cuda_stream)
-
-
 def _nbytes(t) -> int:
-    return 0 if t is None or isinstance(t, int) else t.numel() * t.element_size()
+    return 0 if t is None or isinstance(t, int) else t.nbytes
 
 
 def _check(status: int, what: str) -> None:
@@ -146,50 +169,51 @@ def btc_workspace_bytes(s: btc_shape, rows: int, is_gemm: bool) -> int:
     return lib().btc_workspace_bytes(ctypes.byref(s), rows, int(is_gemm))
 
 
+_pack, _unpack, _gemv, _gemv_static, _gemv_engine, _gemm, _transform, _quantize_rows, _weight_rowsums, _gemm_aq = map(_Entry, (
+    "btc_pack", "btc_unpack", "btc_gemv", "btc_gemv_static", "btc_gemv_engine", "btc_gemm", "btc_transform",
+    "btc_quantize_rows", "btc_weight_rowsums", "btc_gemm_aq"))
+(_transform_prepare, _gemv_transformed, _gemv_multi, _gemv_multi_shapes, _gemv_transformed_multi, _gemv_groups, _assign,
+ _update) = map(_Entry, (
+     "btc_transform_prepare", "btc_gemv_transformed", "btc_gemv_multi", "btc_gemv_multi_shapes",
+     "btc_gemv_transformed_multi", "btc_gemv_groups", "btc_assign", "btc_update"))
+
+
 def btc_pack(s: btc_shape, idx, packed, workspace, stream=None, workspace_bytes: Optional[int] = None) -> None:
-    wb = _nbytes(workspace) if workspace_bytes is None else workspace_bytes
-    _check(lib().btc_pack(_stream(stream), ctypes.byref(s), _ptr(idx), _ptr(packed), _ptr(workspace), wb),
-           "btc_pack")
+    _pack(stream, s, idx, packed, workspace, _nbytes(workspace) if workspace_bytes is None else workspace_bytes)
 
 
 def btc_unpack(s: btc_shape, packed, idx, stream=None) -> None:
-    _check(lib().btc_unpack(_stream(stream), ctypes.byref(s), _ptr(packed), _ptr(idx)), "btc_unpack")
+    _unpack(stream, s, packed, idx)
 
 
 def btc_gemv(s: btc_shape, packed, codebook, alpha, mu, x, batch: int, y, y_dtype: int,
              workspace=None, stream=None, workspace_bytes: Optional[int] = None) -> None:
-    wb = _nbytes(workspace) if workspace_bytes is None else workspace_bytes
-    _check(lib().btc_gemv(_stream(stream), ctypes.byref(s), _ptr(packed), _ptr(codebook), _ptr(alpha), _ptr(mu),
-                          _ptr(x), batch, _ptr(y), y_dtype, _ptr(workspace), wb), "btc_gemv")
+    _gemv(stream, s, packed, codebook, alpha, mu, x, batch, y, y_dtype, workspace,
+          _nbytes(workspace) if workspace_bytes is None else workspace_bytes)
 
 
 def btc_gemv_static(s: btc_shape, packed, codebook, alpha, mu, x, batch: int, y, y_dtype: int, stream=None) -> None:
-    _check(lib().btc_gemv_static(_stream(stream), ctypes.byref(s), _ptr(packed), _ptr(codebook), _ptr(alpha), _ptr(mu),
-                                 _ptr(x), batch, _ptr(y), y_dtype), "btc_gemv_static")
+    _gemv_static(stream, s, packed, codebook, alpha, mu, x, batch, y, y_dtype)
 
 
 def btc_gemv_engine(s: btc_shape, packed, codebook, alpha, mu, x, batch: int, y, y_dtype: int, engine: int,
                     workspace=None, stream=None, workspace_bytes: Optional[int] = None) -> None:
-    wb = _nbytes(workspace) if workspace_bytes is None else workspace_bytes
-    _check(lib().btc_gemv_engine(_stream(stream), ctypes.byref(s), _ptr(packed), _ptr(codebook), _ptr(alpha), _ptr(mu),
-                                 _ptr(x), batch, _ptr(y), y_dtype, _ptr(workspace), wb, engine), "btc_gemv_engine")
+    _gemv_engine(stream, s, packed, codebook, alpha, mu, x, batch, y, y_dtype, workspace,
+                 _nbytes(workspace) if workspace_bytes is None else workspace_bytes, engine)
 
 
 def btc_gemm(s: btc_shape, packed, codebook, alpha, mu, X, x_dtype: int, M: int, Y, y_dtype: int,
              workspace=None, stream=None, workspace_bytes: Optional[int] = None) -> None:
-    wb = _nbytes(workspace) if workspace_bytes is None else workspace_bytes
-    _check(lib().btc_gemm(_stream(stream), ctypes.byref(s), _ptr(packed), _ptr(codebook), _ptr(alpha), _ptr(mu),
-                          _ptr(X), x_dtype, M, _ptr(Y), y_dtype, _ptr(workspace), wb), "btc_gemm")
+    _gemm(stream, s, packed, codebook, alpha, mu, X, x_dtype, M, Y, y_dtype, workspace,
+          _nbytes(workspace) if workspace_bytes is None else workspace_bytes)
 
 
 def btc_transform(X, x_dtype: int, M: int, n1: int, n2: int, sign_bits, P1, P2, Y, y_dtype: int, stream=None) -> None:
-    _check(lib().btc_transform(_stream(stream), _ptr(X), x_dtype, M, n1, n2, _ptr(sign_bits), _ptr(P1), _ptr(P2),
-                               _ptr(Y), y_dtype), "btc_transform")
+    _transform(stream, X, x_dtype, M, n1, n2, sign_bits, P1, P2, Y, y_dtype)
 
 
 def btc_quantize_rows(X, x_dtype: int, M: int, n: int, bits: int, Q, lo, step, qsum=None, stream=None) -> None:
-    _check(lib().btc_quantize_rows(_stream(stream), _ptr(X), x_dtype, M, n, bits, _ptr(Q), _ptr(lo), _ptr(step),
-                                   _ptr(qsum)), "btc_quantize_rows")
+    _quantize_rows(stream, X, x_dtype, M, n, bits, Q, lo, step, qsum)
 
 
 def btc_aq_workspace_bytes(s: BtcShape, M: int) -> int:
@@ -197,15 +221,12 @@ def btc_aq_workspace_bytes(s: BtcShape, M: int) -> int:
 
 
 def btc_weight_rowsums(s: BtcShape, packed, codebook, alpha, mu, wsum, workspace, stream=None) -> None:
-    _check(lib().btc_weight_rowsums(_stream(stream), ctypes.byref(s), _ptr(packed), _ptr(codebook), _ptr(alpha),
-                                    _ptr(mu), _ptr(wsum), _ptr(workspace), _nbytes(workspace)), "btc_weight_rowsums")
+    _weight_rowsums(stream, s, packed, codebook, alpha, mu, wsum, workspace, _nbytes(workspace))
 
 
 def btc_gemm_aq(s: BtcShape, packed, codebook, alpha, mu, wsum, Q, lo, step, M: int, Y, y_dtype: int, workspace,
                 stream=None) -> None:
-    _check(lib().btc_gemm_aq(_stream(stream), ctypes.byref(s), _ptr(packed), _ptr(codebook), _ptr(alpha), _ptr(mu),
-                             _ptr(wsum), _ptr(Q), _ptr(lo), _ptr(step), M, _ptr(Y), y_dtype, _ptr(workspace),
-                             _nbytes(workspace)), "btc_gemm_aq")
+    _gemm_aq(stream, s, packed, codebook, alpha, mu, wsum, Q, lo, step, M, Y, y_dtype, workspace, _nbytes(workspace))
 
 
 def btc_transform_prepared_bytes(n1: int, n2: int) -> int:
@@ -213,8 +234,7 @@ def btc_transform_prepared_bytes(n1: int, n2: int) -> int:
 
 
 def btc_transform_prepare(n1: int, n2: int, P1, P2, prepared, stream=None) -> None:
-    _check(lib().btc_transform_prepare(_stream(stream), n1, n2, _ptr(P1), _ptr(P2), _ptr(prepared), _nbytes(prepared)),
-           "btc_transform_prepare")
+    _transform_prepare(stream, n1, n2, P1, P2, prepared, _nbytes(prepared))
 
 
 def btc_gemv_transformed_workspace_bytes(s: BtcShape) -> int:
@@ -223,51 +243,35 @@ def btc_gemv_transformed_workspace_bytes(s: BtcShape) -> int:
 
 def btc_gemv_transformed(s: BtcShape, packed, codebook, alpha, mu, x, n1: int, n2: int, sign_bits, P1, P2, prepared, y,
                          y_dtype: int, workspace=None, xt_out=None, stream=None) -> None:
-    _check(lib().btc_gemv_transformed(_stream(stream), ctypes.byref(s), _ptr(packed), _ptr(codebook), _ptr(alpha),
-                                      _ptr(mu), _ptr(x), n1, n2, _ptr(sign_bits), _ptr(P1), _ptr(P2), _ptr(prepared),
-                                      _ptr(xt_out), _ptr(y), y_dtype, _ptr(workspace), _nbytes(workspace)),
-           "btc_gemv_transformed")
-
-
-def _ptr_array(ts):
-    return (ctypes.c_void_p * len(ts))(*[_ptr(t).value for t in ts])
+    _gemv_transformed(stream, s, packed, codebook, alpha, mu, x, n1, n2, sign_bits, P1, P2, prepared, xt_out, y, y_dtype,
+                      workspace, _nbytes(workspace))
 
 
 def btc_gemv_multi(s: BtcShape, packed, codebook, alpha, mu, x, y, y_dtype: int, workspace=None, stream=None) -> None:
     """packed, codebook, alpha, mu, y: sequences of the same length (1..4), one entry per matrix."""
-    _check(lib().btc_gemv_multi(_stream(stream), ctypes.byref(s), len(packed), _ptr_array(packed), _ptr_array(codebook),
-                                _ptr_array(alpha), _ptr_array(mu), _ptr(x), _ptr_array(y), y_dtype, _ptr(workspace),
-                                _nbytes(workspace)), "btc_gemv_multi")
+    _gemv_multi(stream, s, len(packed), packed, codebook, alpha, mu, x, y, y_dtype, workspace, _nbytes(workspace))
 
 
 def btc_gemv_multi_shapes(shapes, packed, codebook, alpha, mu, x, y, y_dtype: int, workspace=None, stream=None) -> None:
     """shapes, packed, codebook, alpha, mu, y: sequences of the same length (1..4), one entry per matrix; the shapes
     agree in everything but the number of rows."""
-    arr = (ctypes.POINTER(btc_shape) * len(shapes))(*[ctypes.pointer(s) for s in shapes])
-    _check(lib().btc_gemv_multi_shapes(_stream(stream), arr, len(shapes), _ptr_array(packed), _ptr_array(codebook),
-                                       _ptr_array(alpha), _ptr_array(mu), _ptr(x), _ptr_array(y), y_dtype,
-                                       _ptr(workspace), _nbytes(workspace)), "btc_gemv_multi_shapes")
+    _gemv_multi_shapes(stream, shapes, len(shapes), packed, codebook, alpha, mu, x, y, y_dtype, workspace, _nbytes(workspace))
 
 
 def btc_gemv_transformed_multi(s: BtcShape, packed, codebook, alpha, mu, x, n1: int, n2: int, sign_bits, P1, P2, prepared,
                                y, y_dtype: int, workspace=None, xt_out=None, stream=None) -> None:
     """packed, codebook, alpha, mu, y: sequences of the same length (1..4), one entry per matrix."""
-    _check(lib().btc_gemv_transformed_multi(_stream(stream), ctypes.byref(s), len(packed), _ptr_array(packed),
-                                            _ptr_array(codebook), _ptr_array(alpha), _ptr_array(mu), _ptr(x), n1, n2,
-                                            _ptr(sign_bits), _ptr(P1), _ptr(P2), _ptr(prepared), _ptr(xt_out),
-                                            _ptr_array(y), y_dtype, _ptr(workspace), _nbytes(workspace)),
-           "btc_gemv_transformed_multi")
+    _gemv_transformed_multi(stream, s, len(packed), packed, codebook, alpha, mu, x, n1, n2, sign_bits, P1, P2, prepared,
+                            xt_out, y, y_dtype, workspace, _nbytes(workspace))
 
 
 def btc_gemv_groups(s: BtcShape, packed, codebook, alpha, mu, group_map, ngroups: int, x, y, y_dtype: int,
                     stream=None) -> None:
-    _check(lib().btc_gemv_groups(_stream(stream), ctypes.byref(s), _ptr(packed), _ptr(codebook), _ptr(alpha), _ptr(mu),
-                                 _ptr(group_map), ngroups, _ptr(x), _ptr(y), y_dtype), "btc_gemv_groups")
+    _gemv_groups(stream, s, packed, codebook, alpha, mu, group_map, ngroups, x, y, y_dtype)
 
 
 def btc_assign(vectors, N: int, v: int, codebook, K: int, z, dist2=None, stream=None) -> None:
-    _check(lib().btc_assign(_stream(stream), _ptr(vectors), N, v, _ptr(codebook), K, _ptr(z), _ptr(dist2)),
-           "btc_assign")
+    _assign(stream, vectors, N, v, codebook, K, z, dist2)
 
 
 def btc_update_workspace_bytes(v: int, K: int) -> int:
@@ -276,6 +280,5 @@ def btc_update_workspace_bytes(v: int, K: int) -> int:
 
 def btc_update(vectors, z, N: int, v: int, codebook, K: int, workspace, stream=None,
                workspace_bytes: Optional[int] = None) -> None:
-    wb = _nbytes(workspace) if workspace_bytes is None else workspace_bytes
-    _check(lib().btc_update(_stream(stream), _ptr(vectors), _ptr(z), N, v, _ptr(codebook), K, _ptr(workspace), wb),
-           "btc_update")
+    _update(stream, vectors, z, N, v, codebook, K, workspace,
+            _nbytes(workspace) if workspace_bytes is None else workspace_bytes)

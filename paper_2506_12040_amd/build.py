@@ -1,16 +1,19 @@
-"""Build the HIP library in-tree: csrc/*.hip -> libbtc_hip.so (gfx950 only)."""
+"""Build the HIP library in-tree: csrc/*.hip -> libbtc_hip.so (gfx950 only), and the call path of the Python
+binding: csrc/btc_python.c -> _native.so."""
 from __future__ import annotations
 
 import concurrent.futures
 import glob
 import os
 import subprocess
+import sysconfig
 
 PKG = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(PKG, "csrc")
 INCLUDE = os.path.join(os.path.dirname(PKG), "include")
 LIB = os.path.join(PKG, "libbtc_hip.so")
 OBJ_DIR = os.path.join(PKG, "_build")
+NATIVE = os.path.join(PKG, "_native.so")
 
 HIPCC_FLAGS = [
     "--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC",
@@ -55,6 +58,12 @@ def build(verbose: bool = False, incremental: bool = False, jobs: int = 8) -> st
     err = _run([hipcc, "--offload-arch=gfx950", "-shared", "-fPIC", "-o", LIB, *objs])
     if verbose and err.strip():
         print(err)
+    native_src = os.path.join(CSRC, "btc_python.c")
+    if not (incremental and os.path.exists(NATIVE) and os.path.getmtime(NATIVE) > os.path.getmtime(native_src)):
+        err = _run([os.environ.get("CC", "gcc"), "-O2", "-Wall", "-Wextra", "-shared", "-fPIC", "-fvisibility=hidden",
+                    "-I", sysconfig.get_paths()["include"], "-o", NATIVE, native_src])
+        if verbose and err.strip():
+            print(err)
     return LIB
 
 

@@ -1,7 +1,11 @@
 // Host-side entry points that touch no device memory: shape arithmetic,
 // byte counts, status strings.  (Storage format: Section "Compression
 // Analysis" -- ceil(log2 c) index bits per length-v vector.)
+#include <immintrin.h>
+
 #include <algorithm>
+#include <atomic>
+#include <chrono>
 
 #include "btc_internal.h"
 
@@ -37,6 +41,21 @@ uint32_t* host_word() {
   }
   *(volatile uint32_t*)word.p = 0u;
   return word.p;
+}
+
+btc_status wait_host_word(hipStream_t q, const uint32_t* word) {
+  const volatile uint32_t* w = word;
+  const auto begin = std::chrono::steady_clock::now();
+  for (int n = 0; *w == 0u; ++n) {
+    _mm_pause();
+    // long work in front of it (or an error): give the processor back
+    if ((n & 255) == 255 && std::chrono::steady_clock::now() - begin > std::chrono::microseconds(300)) {
+      if (hipStreamSynchronize(q) != hipSuccess) return BTC_ERR_HIP;
+      break;
+    }
+  }
+  std::atomic_thread_fence(std::memory_order_acquire);
+  return *w == 1u ? BTC_OK : *w == 3u ? BTC_ERR_INDEX_RANGE : BTC_ERR_HIP;
 }
 
 }  // namespace btc

@@ -5,8 +5,10 @@
 // centroids the lowest index wins (the paper leaves ties open; duplicates in the codebook make
 // them common).  Integer work, exact.
 //
-// Two kernels: few different vectors (a table of all 2^v patterns per workgroup), and all pairs on the integer matrix
-// cores.
+// Few different vectors: a table of all 2^v patterns per workgroup (one kernel up to v = 15, one for v = 16).  Otherwise all
+// pairs on the integer matrix cores.
+#include <algorithm>
+
 #include "btc_internal.h"
 
 namespace btc {
@@ -109,7 +111,7 @@ __global__ __launch_bounds__(kThreads) void assign_mfma_kernel(const uint32_t* _
   }
 }
 
-// ---- many vectors (N >= 64 * 2^v, v <= 14): there are only 2^v different ones, so every workgroup first makes a table
+// ---- short vectors (v <= 15): there are only 2^v different ones, so every workgroup first makes a table
 // of all of them -- key  distance << 16 | codeword, the least over the codebook -- and then looks its share of the
 // vectors up.  The table is a distance transform over the v-cube: the entries of the codewords start at distance 0, all
 // others at infinity, and for every bit the two entries that differ in it exchange  key + (1 << 16):  v steps of 2^(v-1)
@@ -160,6 +162,131 @@ __global__ __launch_bounds__(kLutThreads) void assign_lut_kernel(const uint32_t*
   }
 }
 
+// ---- the same for v = 16 and K <= 4096: 65536 keys  distance << ib | codeword  (ib <= 12 index bits) of 16 bits, 128 KB of
+// LDS.  A thread takes 64 entries into registers, two to a register, so that five or six of the bits exchange inside a
+// thread with saturating packed 16-bit arithmetic; three trips through LDS cover the 16 bits (bit by bit through LDS: 16
+// trips).  All ones stands for "further than the key can say": no codebook of 4096 different codewords has such a
+// pattern, but one with many duplicates can, and a vector with that pattern is compared with the codebook directly.
+// About 9 us for the table on every compute unit; 10.2 M vectors against 4096 codewords: 33 us (1751 us as pairs on
+// the matrix cores), 123 MB of it memory; 59 k vectors: 14 us (61 us).
+typedef __attribute__((ext_vector_type(2))) unsigned short u16x2;
+
+__device__ __forceinline__ uint32_t nearer(uint32_t a, uint32_t b, uint32_t step) {      // min(a, b + step), both halves
+  const u16x2 far = __builtin_elementwise_add_sat(__builtin_bit_cast(u16x2, b), __builtin_bit_cast(u16x2, step));
+  return __builtin_bit_cast(uint32_t, __builtin_elementwise_min(__builtin_bit_cast(u16x2, a), far));
+}
+
+// the exchange along bit BIT of the register number
+template <int BIT>
+__device__ __forceinline__ void exchange(uint32_t (&r)[32], uint32_t step) {
+#pragma unroll
+  for (int e = 0; e < 32; ++e) {
+    if (e & (1 << BIT)) continue;
+    const uint32_t a = r[e], b = r[e | (1 << BIT)];
+    r[e] = nearer(a, b, step);
+    r[e | (1 << BIT)] = nearer(b, a, step);
+  }
+}
+
+__device__ __forceinline__ void exchange5(uint32_t (&r)[32], uint32_t step) {
+  exchange<0>(r, step);
+  exchange<1>(r, step);
+  exchange<2>(r, step);
+  exchange<3>(r, step);
+  exchange<4>(r, step);
+}
+
+__device__ __noinline__ uint32_t nearest(uint32_t b, const uint32_t* __restrict__ codebook, int K) {
+  uint32_t best = 0xFFFFFFFFu;
+  for (int k = 0; k < K; ++k) best = min(best, ((uint32_t)__popc((codebook[k] ^ b) & 0xFFFFu) << 16) | (uint32_t)k);
+  return best;
+}
+
+__global__ __launch_bounds__(kLutThreads) void assign_lut16_kernel(const uint32_t* __restrict__ vectors, long long N,
+                                                                  const uint32_t* __restrict__ codebook, int K, int ib,
+                                                                  int32_t* __restrict__ z, int32_t* __restrict__ dist2) {
+  extern __shared__ __align__(16) uint32_t pairs[];            // [2^15]: patterns 2w (low half) and 2w + 1
+  const int tid = threadIdx.x;
+  const long long step = (long long)gridDim.x * kLutThreads * 4;
+  long long i = ((long long)blockIdx.x * kLutThreads + tid) * 4;
+  uint4 w0 = make_uint4(0u, 0u, 0u, 0u), w1 = w0;              // two trips ahead
+  if (i + 3 < N) w0 = *(const uint4*)(vectors + i);
+  if (i + step + 3 < N) w1 = *(const uint4*)(vectors + i + step);
+  uint4* quads = (uint4*)pairs;
+#pragma unroll
+  for (int j = 0; j < 8; ++j) quads[tid + j * kLutThreads] = make_uint4(~0u, ~0u, ~0u, ~0u);
+  __syncthreads();
+  for (int k = tid; k < K; k += kLutThreads) {                 // the lowest codeword of a pattern
+    const uint32_t p = codebook[k] & 0xFFFFu, sh = (p & 1u) * 16u;
+    uint32_t old = pairs[p >> 1];
+    while (((old >> sh) & 0xFFFFu) > (uint32_t)k) {
+      const uint32_t seen = old;
+      old = atomicCAS(&pairs[p >> 1], seen, (seen & ~(0xFFFFu << sh)) | ((uint32_t)k << sh));
+      if (old == seen) break;
+    }
+  }
+  __syncthreads();
+  const uint32_t one = 0x10001u << ib;
+  uint32_t r[32];
+  // bits 0..5: a thread's 64 neighbouring entries; quad j ^ (tid % 8) in place j (bank conflicts), which only reflects bits
+#pragma unroll
+  for (int j = 0; j < 8; ++j) {
+    const uint4 t = quads[tid * 8 + (j ^ (tid & 7))];
+    r[4 * j] = t.x; r[4 * j + 1] = t.y; r[4 * j + 2] = t.z; r[4 * j + 3] = t.w;
+  }
+#pragma unroll
+  for (int e = 0; e < 32; ++e) r[e] = nearer(r[e], __builtin_amdgcn_alignbit(r[e], r[e], 16), one);
+  exchange5(r, one);
+#pragma unroll
+  for (int j = 0; j < 8; ++j)
+    quads[tid * 8 + (j ^ (tid & 7))] = make_uint4(r[4 * j], r[4 * j + 1], r[4 * j + 2], r[4 * j + 3]);
+  __syncthreads();
+  // bits 6..10, then 11..15
+#pragma unroll
+  for (int at = 5; at <= 10; at += 5) {
+    const int base = (tid & ((1 << at) - 1)) | ((tid >> at) << (at + 5));
+#pragma unroll
+    for (int e = 0; e < 32; ++e) r[e] = pairs[base + (e << at)];
+    exchange5(r, one);
+#pragma unroll
+    for (int e = 0; e < 32; ++e) pairs[base + (e << at)] = r[e];
+    __syncthreads();
+  }
+  const uint16_t* table = (const uint16_t*)pairs;
+  const uint32_t index = (1u << ib) - 1u;
+  auto look = [&](uint32_t b, int& k, int& d2) {
+    const uint32_t key = table[b & 0xFFFFu];
+    k = (int)(key & index);
+    d2 = (int)(key >> ib) * 4;
+    if (key == 0xFFFFu) {
+      const uint32_t best = nearest(b, codebook, K);
+      k = (int)(best & 0xFFFFu);
+      d2 = (int)(best >> 16) * 4;
+    }
+  };
+  for (; i < N; i += step) {
+    if (i + 3 < N) {
+      const uint4 b = w0;
+      w0 = w1;
+      if (i + 2 * step + 3 < N) w1 = *(const uint4*)(vectors + i + 2 * step);
+      int4 k, d2;
+      look(b.x, k.x, d2.x);
+      look(b.y, k.y, d2.y);
+      look(b.z, k.z, d2.z);
+      look(b.w, k.w, d2.w);
+      *(int4*)(z + i) = k;
+      if (dist2) *(int4*)(dist2 + i) = d2;
+    } else {
+      for (long long j = i; j < N; ++j) {
+        int k, d2;
+        look(vectors[j], k, d2);
+        z[j] = k;
+        if (dist2) dist2[j] = d2;
+      }
+    }
+  }
+}
+
 }  // namespace assign
 }  // namespace btc
 
@@ -173,10 +300,35 @@ btc_status btc_assign(void* stream, const uint32_t* vectors, int64_t N, int32_t 
   if (N <= 0) return BTC_ERR_SHAPE;
   if (v < 1 || v > 32 || K < 1 || K > 65536) return BTC_ERR_UNSUPPORTED;
   if (!aligned16(vectors) || !aligned16(codebook) || !aligned16(z) || (dist2 && !aligned16(dist2))) return BTC_ERR_ALIGN;
-  if (v <= 14 && N >= (64LL << v)) {
-    const long long want = (N + 4 * kLutThreads - 1) / (4 * kLutThreads);
-    const unsigned grid = (unsigned)(want < 512 ? want : 512);   // two tables per compute unit: 32 waves for the streaming part
+  // Tables pay when the pairs they replace take longer than making them on every compute unit (microseconds; the matrix
+  // cores take 2.4e7 pairs in one, and a wave 60 for its walk through 4096 codewords however few vectors there are).
+  const double pairs_us = std::max((double)N * K / 2.4e7, K * (60.0 / 4096));
+  const double table_us = v == 16 ? 9.0 : v <= 15 ? 0.7 + 2.4e-5 * v * (1 << v) : 1e30;
+  const long long want = (N + 4 * kLutThreads - 1) / (4 * kLutThreads);
+  const bool many = pairs_us > table_us;
+  if (v <= 15 && many) {
+    const unsigned most = v <= 14 ? 512 : 256;     // two tables per compute unit where they fit: 32 waves for the streaming part
+    const unsigned grid = (unsigned)(want < most ? want : most);
+    static bool attr_set = false;  // one-time kernel attribute, not call state
+    if (v > 13 && !attr_set) {
+      if (hipFuncSetAttribute((const void*)assign_lut_kernel, hipFuncAttributeMaxDynamicSharedMemorySize, 4 << 15) != hipSuccess)
+        return BTC_ERR_HIP;
+      attr_set = true;
+    }
     assign_lut_kernel<<<grid, kLutThreads, (size_t)4 << v, (hipStream_t)stream>>>(vectors, (long long)N, v, codebook, K, z, dist2);
+    return launch_status();
+  }
+  if (v == 16 && K <= 4096 && many) {
+    static bool attr_set = false;
+    if (!attr_set) {
+      if (hipFuncSetAttribute((const void*)assign_lut16_kernel, hipFuncAttributeMaxDynamicSharedMemorySize, 2 << 16) != hipSuccess)
+        return BTC_ERR_HIP;
+      attr_set = true;
+    }
+    int ib = 1;
+    while ((1 << ib) < K) ++ib;
+    assign_lut16_kernel<<<(unsigned)(want < 256 ? want : 256), kLutThreads, 2 << 16, (hipStream_t)stream>>>(
+        vectors, (long long)N, codebook, K, ib, z, dist2);
     return launch_status();
   }
   const long long per_block = (long long)(kThreads / 64) * 32 * kCols;

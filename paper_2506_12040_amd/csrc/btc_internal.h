@@ -121,10 +121,12 @@ btc_status gemm_generic(hipStream_t q, const Dims& d, const uint32_t* packed, co
                         const float* alpha, const float* mu, const void* X, int is_bf16, int M, void* Y,
                         int y_dtype, const float* rowsum);
 
-// A word of pinned host memory for the calling thread, set to zero: where the calls that wait (btc_pack, btc_update) have
-// their kernels report an index out of range (reading a word of device memory back costs a staged copy and a second
-// trip).  Null if it cannot be had.
+// A word of pinned host memory for the calling thread, set to zero: where the last kernel of a call that waits (btc_pack,
+// btc_update) reports, once everything the call wrote is in memory, 1 or, after an index out of range, 3.  Null if it
+// cannot be had.
 uint32_t* host_word();
+// Waits for the report and turns it into the call's status.
+btc_status wait_host_word(hipStream_t q, const uint32_t* word);
 
 inline btc_status launch_status() {
   return hipGetLastError() == hipSuccess ? BTC_OK : BTC_ERR_HIP;

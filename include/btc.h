@@ -153,7 +153,7 @@ enum {
   BTC_ENGINE_AUTO = 0,
   BTC_ENGINE_EXPAND = 1,    /* codebook expanded to +-1 pairs, activations in registers            */
   BTC_ENGINE_LUT = 2,       /* per-column tables of partial dot products (the paper's scheme)      */
-  BTC_ENGINE_MFMA_ONE = 3,  /* fp16 matrix cores, one activation row, one kernel                   */
+  BTC_ENGINE_MFMA_ONE = 3,  /* fp16 matrix cores, up to 16 activation rows, one kernel             */
   BTC_ENGINE_MFMA = 4,      /* fp16 matrix cores, up to 16 activation rows, two kernels            */
   BTC_ENGINE_TILED = 5,     /* the prefill kernel on a few rows                                    */
   BTC_ENGINE_GENERIC = 6,   /* any chunk length and index width                                    */

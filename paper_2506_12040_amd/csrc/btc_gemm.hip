@@ -7,6 +7,8 @@
 // so the kernels contract X with the exact +-1 patterns and need sum_k X[m][k].
 #include <hip/hip_fp16.h>
 
+#include <algorithm>
+
 #include "btc_internal.h"
 
 namespace btc {
@@ -74,6 +76,12 @@ btc_status btc_gemm(void* stream, const btc_shape* s, const uint32_t* packed, co
   float* rowsum = (float*)((char*)workspace + 16);
   const int is_bf16 = x_dtype == BTC_BF16;
   const double decode_us = gemm_decode_covers(d, M) ? gemm_decode_estimate_us(d, M) : 1e30;
+  // Up to 16 rows: the one-kernel decode engine of btc_gemv, unless the rows are so long that it walks them in many pieces.
+  if (gemv_few_covers(d, M)) {
+    const double two_kernels_us = gemv_mfma_covers(d, M) ? gemv_mfma_estimate_us(d, M) : 1e30;
+    if (gemv_few_estimate_us(d, M) < std::min(two_kernels_us, decode_us))
+      return gemv_few(q, d, packed, codebook, alpha, mu, X, is_bf16, M, Y, (int)y_dtype);
+  }
   // 17..64 activation rows: the same operand scheme with two or four blocks of activation rows
   // per table read, one pass over the index stream.
   if (gemm_rows_covers(d, M) && gemm_rows_estimate_us(d, M) < decode_us)

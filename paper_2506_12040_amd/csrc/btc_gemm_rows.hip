@@ -221,7 +221,7 @@ __global__ __launch_bounds__(kRWaves * 64) void gemm_rows_kernel(
         for (int w = 0; w < 4; ++w) {
           uint32_t flags;
           asm("v_and_b32 %0, 0x10001, %1" : "=v"(flags) : "v"(a8[r][w].x));
-          asm("v_lshl_or_b32 %0, %1, 15, %2" : "=v"(a2w[r][w]) : "v"(flags), "s"(one2));
+          a2w[r][w] = (flags << 15) | one2;   // (not in assembly: an MFMA may follow at once)
           a8[r][w].x &= 0xFFFEFFFEu;
         }
       }

@@ -3,62 +3,40 @@
 
 #include "btc_internal.h"
 
-// Rough duration in microseconds of one decode pass over the matrix for a single activation
-// row (a fixed chain of round trips plus streaming time; fitted to measurements on 7B-shaped
-// layers).  Compared with the decoding contraction kernel's own estimate to decide whether a
-// batch is served by one pass per row or by one pass of that kernel for all rows.
-static double row_pass_us(const btc::Dims& d) { return 3.5 + 1.8e-6 * (double)d.out * d.wpr * 4; }
-
 namespace btc {
 
-// The dispatcher's choice of engine for a shape and a number of activation rows.
+// The dispatcher's choice of engine for a shape and a number of activation rows.  Figures: microseconds of GPU time per
+// call in a captured graph, on cold copies.
 static int choose_engine(const Dims& d, int batch) {
   const long long bytes = (long long)d.out * d.wpr * 4;
-  int engine = BTC_ENGINE_AUTO;
-  {
-    // One activation row on the tuned settings (v = 9, 10; 7..10 index bits; rows of at most 30720 weights) and a
-    // matrix of 2.5 MiB or more: the engine on the 4-bit matrix cores.  Measured against the engines below on the
-    // LLaMA-2 7B / 13B / 70B projection shapes at 0.7 .. 1.11 bit: 7.5 against 10.5 us on 11008 x 4096, 7.8 against
-    // 11.5 on 8192 x 8192, 15.0 against 21.6 on 28672 x 8192; level at 13824 x 5120 (8.3 us).  On 5120 x 5120
-    // (2.5 MiB) it takes 6.2 us whatever the indices are; the register-resident engine takes 6.2 us on Zipf
-    // indices and 7.0 us on uniform ones (its table reads collide less when few codewords dominate).  Below that
-    // the longer prologue (table and activation operands are built per workgroup) leaves the register-resident
-    // engine ahead (5.4 .. 5.9 against 6.2 us on 4096 x 4096 at 0.9 bit) -- unless the rows are long (6000 weights
-    // or more), where that engine and the table engine fall behind from 1 MiB on (2362 x 7266 at 1.0 bit: 9.8 and
-    // 8.4 against 7.8 us).
-    if (batch == 1 && (bytes >= (5LL << 19) || (bytes >= (1LL << 20) && d.nchunks >= 600)) && gemv_fp4_covers(d))
-      engine = BTC_ENGINE_FP4;
-    else
-    // One row, 9 or 10 index bits, a wide matrix with few enough rows: the single-kernel variant of the
-    // matrix-core engine (measured on 4096 x 11008 at 9 bits: 8.6 us against 11.4 for the table engine; at 7 or
-    // 8 bits, or with many rows, the other engines stay ahead).
-    if (batch == 1 && d.b >= 9 && d.nchunks >= 1024 && d.out <= 6144 && gemv_mfma_one_covers(d))
-      engine = BTC_ENGINE_MFMA_ONE;
-    else if (gemv_mfma_covers(d, batch) &&
-             (batch == 1 ? ((d.b >= 9 && d.nchunks >= 2048 && bytes >= (16LL << 20)) || (d.b == 10 && bytes >= (8LL << 20)))
-                         : batch * row_pass_us(d) > gemv_mfma_estimate_us(d, batch)))
-      // Several activation rows on a supported setting: one pass of the matrix-core engine serves them all
-      // (unless the matrix is so small that a pass per row is still quicker).  A single row goes there too
-      // when the matrix is large and so wide that the table engine cannot use its streaming kernel, and for
-      // every large matrix with 10-bit indices (128 KB table: one workgroup per compute unit only).
-      engine = BTC_ENGINE_MFMA;
-    else if (batch > 1 && gemm_decode_covers(d, batch) && batch * row_pass_us(d) > gemm_decode_estimate_us(d, batch))
-      engine = BTC_ENGINE_TILED;
-    else if ((bytes < (3LL << 20) || !lut_engine_covers(d)) && expand_engine_covers(d))
-      // Small matrices are bound by the chain of memory round trips: the register-resident engine has the
-      // shortest one.  Larger ones are bound by LDS and ALU throughput, where the table engine is lighter.
-      engine = BTC_ENGINE_EXPAND;
-    else if (lut_engine_covers(d))
-      engine = BTC_ENGINE_LUT;
-    else if (batch == 1 && gemv_code_covers(d))
-      // long vectors or large codebooks (no tuned engine has tables for them): the codebook itself in LDS
-      // (4096 x 4096 at v = 16 with 65536 centroids: 32 us with the fallback kernel)
-      engine = BTC_ENGINE_CODE;
-    else
-      engine = BTC_ENGINE_GENERIC;
+  if (batch > 1 && gemv_few_covers(d, batch))
+    // Several activation rows: decoding the indices is the cost, and one pass serves all the rows.  One kernel where the
+    // activations fit LDS in few pieces; the engine whose column tiles meet in a second kernel where they do not
+    // (4096 x 4096 at 0.9 bit, 2 / 4 / 8 / 16 rows: 6.2 / 7.1 / 8.5 / 12.2 us against 8.0 / 8.1 / 8.6 / 9.5; 16 rows of
+    // 11008: 23 against 12 us).  Two passes of a single-row engine take longer on any matrix.
+    return gemv_mfma_covers(d, batch) && gemv_mfma_estimate_us(d, batch) < gemv_few_estimate_us(d, batch) ? BTC_ENGINE_MFMA
+                                                                                                          : BTC_ENGINE_MFMA_ONE;
+  if (batch == 1) {
+    // One activation row.  Small matrices are bound by the chain of memory round trips, and the register-resident engine
+    // has the shortest one: 3.3 us up to 0.1 MB, level with the engine on the 4-bit matrix cores at 0.85 MB (4.9 us) and
+    // far behind it from there on (1.4 MB: 5.6 against 4.4, 1.9 MB: 7.7 against 4.4).  It takes even rows only.
+    if (gemv_fp4_covers(d) && (bytes >= 850000 || !expand_engine_covers(d))) return BTC_ENGINE_FP4;
+    // Longer rows than that engine takes, in a large matrix: the table engine cannot use its streaming kernel there, and
+    // with 10-bit indices its table leaves one workgroup per compute unit only (20595 x 28516 at 1.11 bit: 115 against 57
+    // us; 74 with column tiles and a second kernel).
+    if (gemv_few_covers(d, batch) &&
+        ((d.b >= 9 && d.nchunks >= 2048 && bytes >= (16LL << 20)) || (d.b == 10 && bytes >= (8LL << 20))))
+      return BTC_ENGINE_MFMA_ONE;
+  } else if (gemm_decode_covers(d, batch) && batch * (3.5 + 1.8e-6 * bytes) > gemm_decode_estimate_us(d, batch)) {
+    return BTC_ENGINE_TILED;             // (against a pass per row)
   }
-
-  return engine;
+  if ((bytes < (3LL << 20) || !lut_engine_covers(d)) && expand_engine_covers(d)) return BTC_ENGINE_EXPAND;
+  // larger ones are bound by LDS and ALU throughput, where the table engine is lighter
+  if (lut_engine_covers(d)) return BTC_ENGINE_LUT;
+  // long vectors or large codebooks (no tuned engine has tables for them): the codebook itself in LDS
+  // (4096 x 4096 at v = 16 with 65536 centroids: 32 us with the fallback kernel)
+  if (batch == 1 && gemv_code_covers(d)) return BTC_ENGINE_CODE;
+  return BTC_ENGINE_GENERIC;
 }
 
 // Whether an engine parks anything in the caller's workspace.
@@ -98,8 +76,8 @@ static btc_status gemv_dispatch(int engine, void* stream, const btc_shape* s, co
 
   switch (engine) {
     case BTC_ENGINE_MFMA_ONE:
-      if (batch != 1 || !gemv_mfma_one_covers(d)) return BTC_ERR_UNSUPPORTED;
-      return gemv_mfma_one(q, d, packed, codebook, alpha, mu, x, y, y_is_f32);
+      if (!gemv_few_covers(d, batch)) return BTC_ERR_UNSUPPORTED;
+      return gemv_few(q, d, packed, codebook, alpha, mu, x, /*is_bf16=*/0, batch, y, (int)y_dtype);
     case BTC_ENGINE_MFMA: {
       if (!gemv_mfma_covers(d, batch)) return BTC_ERR_UNSUPPORTED;
       const size_t off = gemv_table_region_bytes(d);

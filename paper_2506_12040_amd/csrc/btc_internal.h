@@ -69,6 +69,12 @@ btc_status gemv_mfma(hipStream_t q, const Dims& d, const uint32_t* packed, const
                      const float* alpha, const float* mu, const void* x, int is_bf16, int batch, void* y,
                      int y_dtype, void* workspace);
 
+// The same operand scheme in one kernel (btc_gemv_few.hip): a workgroup walks all columns.
+bool gemv_few_covers(const Dims& d, int batch);
+double gemv_few_estimate_us(const Dims& d, int batch);
+btc_status gemv_few(hipStream_t q, const Dims& d, const uint32_t* packed, const uint32_t* codebook, const float* alpha,
+                    const float* mu, const void* x, int is_bf16, int batch, void* y, int y_dtype);
+
 // Second pass of the engines above and below: y = alpha * (sum of `n_ct` partial-sum planes
 // [n_ct][rows][out]) + mu * (sum of `n_ct` row-sum entries, one copy of [n_ct][xstride] per block of
 // 256 outputs); clears what it reads.
@@ -82,11 +88,6 @@ double gemm_rows_estimate_us(const Dims& d, int M);
 btc_status gemm_rows(hipStream_t q, const Dims& d, const uint32_t* packed, const uint32_t* codebook,
                      const float* alpha, const float* mu, const void* X, int is_bf16, int M, void* Y, int y_dtype,
                      void* workspace);
-
-// The same operand scheme for one activation row in a single kernel (16 weight rows per workgroup).
-bool gemv_mfma_one_covers(const Dims& d);
-btc_status gemv_mfma_one(hipStream_t q, const Dims& d, const uint32_t* packed, const uint32_t* codebook,
-                         const float* alpha, const float* mu, const void* x, void* y, int y_is_f32);
 
 // The same scheme on int8 activation codes with the integer matrix cores (btc_gemm_wide_i8.hip):
 //   Y = step * (alpha * <signs, codes> + mu * sum(codes)) + lo * wsum

@@ -30,22 +30,31 @@ __device__ __forceinline__ float widen16(uint16_t h, int is_bf16) {
   return __half2float(__builtin_bit_cast(__half, h));
 }
 
-// One workgroup per activation row, eight elements per load when the row allows it (n % 8 == 0; rows are
-// then 16-byte aligned).  The decision arithmetic is fp32, one IEEE operation per step, in this order:
+// One workgroup per activation row.  Rows of a multiple of eight elements (16-byte aligned then) stay in registers, P pieces
+// of eight per thread, so that memory is read once with every load under way; P = 0: element by element, twice.  The
+// decision arithmetic is fp32, one IEEE operation per step, in this order:
 // t = x - lo;  r = t / step;  q = round-to-nearest-even(r) clamped to the grid.
-template <bool VEC>
-__global__ __launch_bounds__(kThreads) void quantize_rows_kernel(const uint16_t* __restrict__ X, int is_bf16, int n,
-                                                                 int bits, uint8_t* __restrict__ Q,
-                                                                 float* __restrict__ lo, float* __restrict__ step,
-                                                                 float* __restrict__ qsum) {
-  __shared__ float red_min[kThreads / 64], red_max[kThreads / 64], red_sum[kThreads / 64];
+template <int THREADS, int P>
+__global__ __launch_bounds__(THREADS) void quantize_rows_kernel(const uint16_t* __restrict__ X, int is_bf16, int n,
+                                                                int bits, uint8_t* __restrict__ Q,
+                                                                float* __restrict__ lo, float* __restrict__ step,
+                                                                float* __restrict__ qsum) {
+  constexpr int kWaves = THREADS / 64;
+  __shared__ float red_min[kWaves], red_max[kWaves], red_sum[kWaves];
   const int m = blockIdx.x, tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const uint16_t* x = X + (size_t)m * n;
-  float mn = widen16(x[0], is_bf16), mx = mn;
-  if (VEC) {
-    for (int k = tid; k < n / 8; k += kThreads) {
-      const uint4 v = ((const uint4*)x)[k];
-      const uint32_t w[4] = {v.x, v.y, v.z, v.w};
+  uint4 v[P > 0 ? P : 1];
+  float mn, mx;
+  if constexpr (P > 0) {
+#pragma unroll
+    for (int u = 0; u < P; ++u) {                        // (threads behind the end repeat the last piece)
+      const int k = tid + u * THREADS;
+      v[u] = ((const uint4*)x)[k < n / 8 ? k : n / 8 - 1];
+    }
+    mn = mx = widen16((uint16_t)v[0].x, is_bf16);
+#pragma unroll
+    for (int u = 0; u < P; ++u) {
+      const uint32_t w[4] = {v[u].x, v[u].y, v[u].z, v[u].w};
 #pragma unroll
       for (int e = 0; e < 8; ++e) {
         const float f = widen16((uint16_t)(w[e >> 1] >> (16 * (e & 1))), is_bf16);
@@ -54,10 +63,11 @@ __global__ __launch_bounds__(kThreads) void quantize_rows_kernel(const uint16_t*
       }
     }
   } else {
-    for (int k = tid; k < n; k += kThreads) {
-      const float v = widen16(x[k], is_bf16);
-      mn = fminf(mn, v);
-      mx = fmaxf(mx, v);
+    mn = mx = widen16(x[0], is_bf16);
+    for (int k = tid; k < n; k += THREADS) {
+      const float f = widen16(x[k], is_bf16);
+      mn = fminf(mn, f);
+      mx = fmaxf(mx, f);
     }
   }
 #pragma unroll
@@ -71,13 +81,17 @@ __global__ __launch_bounds__(kThreads) void quantize_rows_kernel(const uint16_t*
   }
   __syncthreads();
 #pragma unroll
-  for (int w = 0; w < kThreads / 64; ++w) {
+  for (int w = 0; w < kWaves; ++w) {
     mn = fminf(mn, red_min[w]);
     mx = fmaxf(mx, red_max[w]);
   }
   const float levels = (float)((1 << bits) - 1);
   const float range = mx - mn;
   const float st = range > 0.0f ? range / levels : 1.0f;
+  if (tid == 0) {
+    lo[m] = mn;
+    step[m] = st;
+  }
   float sum = 0.f;                                       // integers: exact in any order
   // The decision is rint(t / step) with an IEEE division.  t * (1 / step) differs from the quotient by at most
   // a few 2^-24 of it, less than 1e-4 on a grid of 255 levels, so it rounds to the same integer unless it lies
@@ -92,18 +106,21 @@ __global__ __launch_bounds__(kThreads) void quantize_rows_kernel(const uint16_t*
     sum += r;
     return (uint32_t)(int)r;
   };
-  if (VEC) {
-    for (int k = tid; k < n / 8; k += kThreads) {        // (a second read of the row: it is in the L2)
-      const uint4 v = ((const uint4*)x)[k];
-      const uint32_t w[4] = {v.x, v.y, v.z, v.w};
+  if constexpr (P > 0) {
+#pragma unroll
+    for (int u = 0; u < P; ++u) {
+      const int k = tid + u * THREADS;
+      if (k >= n / 8) continue;
+      const uint32_t w[4] = {v[u].x, v[u].y, v[u].z, v[u].w};
       uint32_t o[2] = {0u, 0u};
 #pragma unroll
       for (int e = 0; e < 8; ++e) o[e >> 2] |= code((uint16_t)(w[e >> 1] >> (16 * (e & 1)))) << (8 * (e & 3));
       ((uint2*)(Q + (size_t)m * n))[k] = make_uint2(o[0], o[1]);
     }
   } else {
-    for (int k = tid; k < n; k += kThreads) Q[(size_t)m * n + k] = (uint8_t)code(x[k]);
+    for (int k = tid; k < n; k += THREADS) Q[(size_t)m * n + k] = (uint8_t)code(x[k]);
   }
+  if (!qsum) return;
 #pragma unroll
   for (int o = 32; o > 0; o >>= 1) sum += __shfl_xor(sum, o, 64);
   if (lane == 0) red_sum[wave] = sum;
@@ -111,11 +128,16 @@ __global__ __launch_bounds__(kThreads) void quantize_rows_kernel(const uint16_t*
   if (tid == 0) {
     float s = 0.f;
 #pragma unroll
-    for (int w = 0; w < kThreads / 64; ++w) s += red_sum[w];
-    lo[m] = mn;
-    step[m] = st;
-    if (qsum) qsum[m] = s;
+    for (int w = 0; w < kWaves; ++w) s += red_sum[w];
+    qsum[m] = s;
   }
+}
+
+template <int THREADS, int P>
+static btc_status quantize(hipStream_t q, const void* X, int is_bf16, int M, int n, int bits, uint8_t* Q, float* lo, float* step,
+                           float* qsum) {
+  quantize_rows_kernel<THREADS, P><<<M, THREADS, 0, q>>>((const uint16_t*)X, is_bf16, n, bits, Q, lo, step, qsum);
+  return launch_status();
 }
 
 // codes -> the same integers as fp16 numbers (exact), the operand format of the contraction kernels
@@ -179,13 +201,18 @@ btc_status btc_quantize_rows(void* stream, const void* X, btc_dtype x_dtype, int
   if (M <= 0 || n <= 0) return BTC_ERR_SHAPE;
   if ((bits != 8 && bits != 4) || (x_dtype != BTC_F16 && x_dtype != BTC_BF16) || n > aq::kMaxIn) return BTC_ERR_UNSUPPORTED;
   if (!aligned16(X) || !aligned16(Q) || !aligned16(lo) || !aligned16(step) || (qsum && !aligned16(qsum))) return BTC_ERR_ALIGN;
-  if (n % 8 == 0)
-    aq::quantize_rows_kernel<true><<<M, aq::kThreads, 0, (hipStream_t)stream>>>((const uint16_t*)X, x_dtype == BTC_BF16, n,
-                                                                                 bits, Q, lo, step, qsum);
-  else
-    aq::quantize_rows_kernel<false><<<M, aq::kThreads, 0, (hipStream_t)stream>>>((const uint16_t*)X, x_dtype == BTC_BF16, n,
-                                                                                  bits, Q, lo, step, qsum);
-  return launch_status();
+  const hipStream_t q = (hipStream_t)stream;
+  const int is_bf16 = x_dtype == BTC_BF16;
+  // Few rows: the call is one row's chain of latencies, shortest with few pieces per thread (8 rows of 10496: 7 -> 4 us).  Many: as
+  // many rows per compute unit as its registers hold (1024 x 5120: 9.8 -> 7.9 us).
+  if (n % 8 != 0) return aq::quantize<256, 0>(q, X, is_bf16, M, n, bits, Q, lo, step, qsum);
+  if (M < 512) {
+    if (n <= 8 * 1024) return aq::quantize<1024, 1>(q, X, is_bf16, M, n, bits, Q, lo, step, qsum);
+    if (n <= 16 * 1024) return aq::quantize<1024, 2>(q, X, is_bf16, M, n, bits, Q, lo, step, qsum);
+  }
+  if (n <= 3 * 2048) return aq::quantize<256, 3>(q, X, is_bf16, M, n, bits, Q, lo, step, qsum);
+  if (n <= 8 * 2048) return aq::quantize<256, 8>(q, X, is_bf16, M, n, bits, Q, lo, step, qsum);
+  return aq::quantize<1024, 8>(q, X, is_bf16, M, n, bits, Q, lo, step, qsum);
 }
 
 size_t btc_aq_workspace_bytes(const btc_shape* s, int32_t M) {
@@ -243,6 +270,8 @@ btc_status btc_gemm_aq(void* stream, const btc_shape* s, const uint32_t* packed,
   hipStream_t q = (hipStream_t)stream;
   {
     const Dims d = dims_of(*s);
+    if (gemv_few_covers(d, M))
+      return gemm_few_codes(q, d, packed, codebook, alpha, mu, wsum, Q, lo, step, M, Y, (int)y_dtype);
     if (M > 16 && gemm_decode_i8_covers(d, M))
       return gemm_decode_i8(q, d, packed, codebook, alpha, mu, wsum, Q, lo, step, M, Y, (int)y_dtype, workspace,
                             workspace_bytes);

@@ -75,6 +75,11 @@ double gemv_few_estimate_us(const Dims& d, int batch);
 btc_status gemv_few(hipStream_t q, const Dims& d, const uint32_t* packed, const uint32_t* codebook, const float* alpha,
                     const float* mu, const void* x, int is_bf16, int batch, void* y, int y_dtype);
 
+// The same on up to 16 rows of 8-bit codes (btc_gemm_aq):  Y = step * (alpha * <signs, codes> + mu * sum(codes)) + lo * wsum
+btc_status gemm_few_codes(hipStream_t q, const Dims& d, const uint32_t* packed, const uint32_t* codebook, const float* alpha,
+                          const float* mu, const float* wsum, const uint8_t* Q, const float* lo, const float* step, int M,
+                          void* Y, int y_dtype);
+
 // Second pass of the engines above and below: y = alpha * (sum of `n_ct` partial-sum planes
 // [n_ct][rows][out]) + mu * (sum of `n_ct` row-sum entries, one copy of [n_ct][xstride] per block of
 // 256 outputs); clears what it reads.

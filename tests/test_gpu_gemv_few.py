@@ -1,7 +1,7 @@
 """GPU parity of the one-kernel engine for few activation rows (btc_gemv_few.hip) where it changes over: rows of odd length
 (activations that start inside a word), the numbers of rows around its four widths, rows around a super-group and around
 one and several pieces of activations in LDS, outputs around a workgroup's share; fp16 through btc_gemv, bf16 through
-btc_gemm."""
+btc_gemm, 8-bit codes (rows that start on any byte) through btc_gemm_aq."""
 import numpy as np
 import pytest
 
@@ -43,6 +43,27 @@ def test_gemm_bf16(G, oracle, out, n_in, v, K, M, y):
     ref = xb.double() @ W.T
     err = (Y.payload.double().cpu().reshape(M, out) - ref).norm() / ref.norm()
     assert err < {"bf16": 4e-3, "f32": 1e-5, "f16": 1e-3}[y]
+
+
+@pytest.mark.parametrize("out,n_in,v,K,M", [(1, 3, 10, 256, 1), (65, 641, 10, 512, 2), (130, 1283, 10, 128, 3), (33, 577, 9, 1024, 4),
+                                           (200, 5762, 10, 256, 7), (70, 2303, 9, 512, 16), (47, 2561, 10, 600, 15)])
+def test_codes(G, oracle, out, n_in, v, K, M):
+    import torch
+    B = G.B
+    print(f"few, codes out={out} in={n_in} v={v} K={K} M={M}", flush=True)
+    layer, _ = S.make_case(7, out, n_in, v, K, M, dist="uniform")
+    dl = G.DeviceLayer(layer, oracle)
+    rng = np.random.default_rng(M)
+    Q = rng.integers(0, 256, size=(M, n_in), dtype=np.uint8)
+    lo, step, wsum = (rng.standard_normal(n).astype(np.float32) for n in (M, M, out))
+    Y = G.GuardedOutput(M, out, torch.float32)
+    ws = torch.empty(B.btc_aq_workspace_bytes(dl.shape, M), dtype=torch.uint8, device="cuda")
+    B.btc_gemm_aq(dl.shape, dl.packed, dl.codebook, dl.alpha, dl.mu, G.dev(wsum), G.dev(Q), G.dev(lo), G.dev(step), M, Y.payload,
+                  B.BTC_F32, ws)
+    Y.check_guards()
+    ref = step[:, None].astype(np.float64) * (Q.astype(np.float64) @ layer_dense(layer).T) + lo[:, None].astype(np.float64) * wsum
+    got = Y.payload.double().cpu().numpy().reshape(M, out)
+    assert np.linalg.norm(got - ref) < 1e-5 * np.linalg.norm(ref)
 
 
 def layer_dense(layer):

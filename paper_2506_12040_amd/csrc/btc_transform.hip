@@ -18,15 +18,15 @@
 // fixed order: deterministic.  Two shapes of this kernel: for a few rows (decode) the call is
 // a chain of latencies, so a workgroup has 1024 threads and every dot product of both stages is
 // cut into KS = 4 pieces held by neighbouring lanes, whose sums meet by two cross-lane additions;
-// for many rows 256 threads, whole dot products,
+// for more rows than the matrix-core kernel can address 256 threads, whole dot products,
 // four columns per thread, and the rows are dealt to about five workgroups per compute unit.
-// Every global load of a phase is issued before the first one is used.  Many rows of bf16
-// activations (prefill) take the matrix-core kernel further down instead.
+// Every global load of a phase is issued before the first one is used.  More than a few rows
+// (prefill) take the matrix-core kernel of btc_transform_mfma.h instead.
 #include <hip/hip_fp16.h>
 
 #include <type_traits>
 
-#include "btc_internal.h"
+#include "btc_transform_mfma.h"
 
 namespace btc {
 namespace transform {
@@ -264,243 +264,6 @@ __global__ __launch_bounds__(kThreads * KS) void transform_kernel(const uint16_t
   }
 }
 
-// ---------------------------------------------------------------------------------------
-// Many rows of bf16 activations (prefill): the two stages are small dense contractions and
-// run on the matrix cores (MFMA 32x32x16 bf16, fp32 accumulate).  A wave owns one row of X
-// and one block of 32 columns j2:
-//   stage 1:  D1[i1][j2] = sum_i2 (sigma x)[i1][i2] P2[i2][j2]    A = the row itself, read from
-//             global memory in operand layout (16 bytes per lane, signs applied in registers);
-//             B = P2 from LDS
-//   stage 2:  Z[j1][j2]  = sum_i1 P1[i1][j1] D1[i1][j2]           A = P1^T from LDS; B = D1 as it
-//             sits in the accumulators: a lane of D1 holds column j2 = lane % 32 and the 16 rows
-//             8 (e / 4) + 4 (lane / 32) + e % 4, which is a valid B operand once the contraction
-//             index of a 16-row step is permuted the same way in A -- P1^T is staged in that order.
-// The fp32 factors and the fp32 D1 enter as sums of three bf16 numbers (24 bits); products whose
-// weight is below 2^-24 are dropped, so the result has the accuracy of the fp32 kernel above.
-// The activations are bf16 already and enter exactly.
-typedef __attribute__((ext_vector_type(8))) __bf16 bf16x8;
-typedef __attribute__((ext_vector_type(16))) float f32x16;
-
-// float -> bf16 bit pattern, round to nearest even (the hardware conversion of gfx950)
-__device__ __forceinline__ uint32_t bf16_rne(float v) {
-  return (uint32_t)__builtin_bit_cast(uint16_t, (__bf16)v);
-}
-
-// v = p0 + p1 + p2 up to 2^-24 relative, each a bf16 bit pattern
-__device__ __forceinline__ void split3(float v, uint32_t& p0, uint32_t& p1, uint32_t& p2) {
-  p0 = bf16_rne(v);
-  float r = v - __uint_as_float(p0 << 16);
-  p1 = bf16_rne(r);
-  r -= __uint_as_float(p1 << 16);
-  p2 = bf16_rne(r);
-}
-
-__device__ __forceinline__ f32x16 mfma32(const uint4& a, const uint4& b, const f32x16& c) {
-  return __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, a), __builtin_bit_cast(bf16x8, b), c, 0, 0, 0);
-}
-
-// f(integral_constant<int, I>) for I = Begin .. End - 1, fully unrolled
-template <int Begin, int End, class F>
-__device__ __forceinline__ void static_for_it(F&& f) {
-  if constexpr (Begin < End) {
-    f(std::integral_constant<int, Begin>{});
-    static_for_it<Begin + 1, End>(f);
-  }
-}
-
-// IT = ceil(n1 / 32): blocks of 32 rows i1 (and of 32 rows j1).  Needs n2 % 16 == 0.
-// waves per workgroup: with three or four blocks the operands of P1 fill most of LDS (one workgroup per compute
-// unit), so the workgroup is made twice as large to keep two waves per SIMD
-template <int IT>
-constexpr int mfma_waves() { return IT <= 2 ? 4 : 8; }
-
-// NP: bf16 parts per fp32 operand.  Three (24 bits) for fp32 output; two (16 bits, 2^-17 relative) when the output
-// is rounded to fp16 or bf16 anyway (2^-11 / 2^-8): 2 instead of 3 MFMAs per step in stage 1, 3 instead of 6 in stage 2.
-template <int IT, int NP>
-__global__ __launch_bounds__(64 * mfma_waves<IT>()) void transform_mfma_kernel(const uint16_t* __restrict__ X, int M, int n1, int n2,
-                                                                 const uint32_t* __restrict__ sign_bits,
-                                                                 const float* __restrict__ P1,
-                                                                 const float* __restrict__ P2, void* __restrict__ Y,
-                                                                 int y_dtype, int p2_bytes) {
-  constexpr int KS1 = 2 * IT;                // 16-row steps of stage 2
-  constexpr int NWV = mfma_waves<IT>(), NT = 64 * NWV;
-  extern __shared__ __align__(16) unsigned char smem[];
-  uint4* P2op = (uint4*)smem;                // [step][part][lane]: B operands of stage 1
-  uint4* P1op = (uint4*)(smem + p2_bytes);   // [block j1][step][part][lane]: A operands of stage 2
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  const int l32 = lane & 31, h = lane >> 5;
-  const int n = n1 * n2, KS2 = n2 >> 4;
-  const int j2 = blockIdx.x * 32 + l32;
-
-  for (int it = tid; it < KS2 * 64; it += NT) {
-    const int ks = it >> 6, ln = it & 63, c = blockIdx.x * 32 + (ln & 31), hh = ln >> 5;
-    uint32_t q[3][8];
-#pragma unroll
-    for (int e = 0; e < 8; ++e) {
-      const int i2 = 16 * ks + 8 * hh + e;
-      split3(c < n2 ? P2[(size_t)i2 * n2 + c] : 0.f, q[0][e], q[1][e], q[2][e]);
-    }
-#pragma unroll
-    for (int p = 0; p < 3; ++p)
-      P2op[(ks * 3 + p) * 64 + ln] = make_uint4(q[p][0] | q[p][1] << 16, q[p][2] | q[p][3] << 16,
-                                               q[p][4] | q[p][5] << 16, q[p][6] | q[p][7] << 16);
-  }
-  for (int it = tid; it < IT * KS1 * 64; it += NT) {
-    const int ln = it & 63, ks = (it >> 6) % KS1, jt = (it >> 6) / KS1;
-    const int j1 = jt * 32 + (ln & 31), hh = ln >> 5;
-    uint32_t q[3][8];
-#pragma unroll
-    for (int e = 0; e < 8; ++e) {
-      const int i1 = 16 * ks + 8 * (e >> 2) + 4 * hh + (e & 3);   // the row of D1 that element e of a lane's step holds
-      split3((i1 < n1 && j1 < n1) ? P1[(size_t)i1 * n1 + j1] : 0.f, q[0][e], q[1][e], q[2][e]);
-    }
-#pragma unroll
-    for (int p = 0; p < 3; ++p)
-      P1op[((jt * KS1 + ks) * 3 + p) * 64 + ln] = make_uint4(q[p][0] | q[p][1] << 16, q[p][2] | q[p][3] << 16,
-                                                            q[p][4] | q[p][5] << 16, q[p][6] | q[p][7] << 16);
-  }
-  __syncthreads();
-
-  const uint8_t* sign_bytes = (const uint8_t*)sign_bits;   // byte k / 8 holds the bits of channels k .. k + 7
-  // One block of 32 rows i1 at a time: its stage 1 (all steps over i2), the split of its 32 x 32 result, and its
-  // share of stage 2 for every block j1 -- so only one block of the intermediate is alive, next to the IT
-  // accumulators of the output.  A operands of stage 1 come straight from global memory, PD steps ahead: slot u of
-  // the ring holds step ks0 + u of the current chunk of PD steps; once used it is refilled with step ks0 + PD + u
-  // of the same block or, in a block's last chunk, with step u of the next block (of the wave's next row after
-  // the last block), so the loads always fly during the arithmetic of the block before.
-  constexpr int PD = 4;
-  const int stride = NWV * gridDim.y;
-  auto load_a = [&](int mm, int it, int ks, uint4& a, uint32_t& sg) __attribute__((always_inline)) {
-    const int i1 = min(it * 32 + l32, n1 - 1);                 // rows past the end: a valid row, zeroed below
-    const int k = i1 * n2 + 16 * ks + 8 * h;
-    a = *(const uint4*)(X + (size_t)mm * n + k);
-    sg = sign_bytes[k >> 3];
-  };
-  uint4 ring[PD];
-  uint32_t rsg[PD];
-  const int m_first = blockIdx.y * NWV + wave;
-  if (m_first < M) {
-#pragma unroll
-    for (int u = 0; u < PD; ++u)
-      if (u < KS2) load_a(m_first, 0, u, ring[u], rsg[u]);
-  }
-  for (int m = m_first; m < M; m += stride) {
-    f32x16 z[IT];
-#pragma unroll
-    for (int jt = 0; jt < IT; ++jt)
-#pragma unroll
-      for (int e = 0; e < 16; ++e) z[jt][e] = 0.f;
-    static_for_it<0, IT>([&](auto it_c) {
-      constexpr int it = decltype(it_c)::value;
-      f32x16 d1;
-#pragma unroll
-      for (int e = 0; e < 16; ++e) d1[e] = 0.f;
-      const bool row_ok = it * 32 + l32 < n1;
-      for (int ks0 = 0; ks0 < KS2; ks0 += PD) {
-        const bool last_chunk = ks0 + PD >= KS2;
-#pragma unroll
-        for (int u = 0; u < PD; ++u) {
-          const int ks = ks0 + u;
-          if (ks < KS2) {
-            const uint32_t minus = ~rsg[u] & 0xFFu;              // bit e set: element e changes sign
-            uint4 a = ring[u];
-            a.x ^= ((minus & 1u) << 15) | ((minus & 2u) << 30);
-            a.y ^= ((minus & 4u) << 13) | ((minus & 8u) << 28);
-            a.z ^= ((minus & 16u) << 11) | ((minus & 32u) << 26);
-            a.w ^= ((minus & 64u) << 9) | ((minus & 128u) << 24);
-            if (!row_ok) a = make_uint4(0u, 0u, 0u, 0u);
-            d1 = mfma32(a, P2op[(ks * 3 + 0) * 64 + lane], d1);
-            d1 = mfma32(a, P2op[(ks * 3 + 1) * 64 + lane], d1);
-            if constexpr (NP == 3) d1 = mfma32(a, P2op[(ks * 3 + 2) * 64 + lane], d1);
-          }
-          if (ks + PD < KS2) {
-            load_a(m, it, ks + PD, ring[u], rsg[u]);
-          } else if (last_chunk && u < KS2) {
-            if (it + 1 < IT) load_a(m, it + 1, u, ring[u], rsg[u]);
-            else if (m + stride < M) load_a(m + stride, 0, u, ring[u], rsg[u]);
-          }
-        }
-      }
-      // the block as three bf16 parts, in B-operand form: step s2 takes elements 8 s2 .. 8 s2 + 7
-#pragma unroll
-      for (int s2 = 0; s2 < 2; ++s2) {
-        uint32_t q[3][8];
-#pragma unroll
-        for (int e = 0; e < 8; ++e) split3(d1[8 * s2 + e], q[0][e], q[1][e], q[2][e]);
-        uint4 y[3];
-#pragma unroll
-        for (int p = 0; p < 3; ++p)
-          y[p] = make_uint4(q[p][0] | q[p][1] << 16, q[p][2] | q[p][3] << 16, q[p][4] | q[p][5] << 16, q[p][6] | q[p][7] << 16);
-#pragma unroll
-        for (int jt = 0; jt < IT; ++jt) {
-          const uint4* ap = P1op + ((jt * KS1 + 2 * it + s2) * 3) * 64 + lane;
-          const uint4 a0 = ap[0], a1 = ap[64];
-          if constexpr (NP == 3) {                               // small terms first
-            z[jt] = mfma32(ap[128], y[0], z[jt]);
-            z[jt] = mfma32(a1, y[1], z[jt]);
-            z[jt] = mfma32(a0, y[2], z[jt]);
-          }
-          z[jt] = mfma32(a1, y[0], z[jt]);
-          z[jt] = mfma32(a0, y[1], z[jt]);
-          z[jt] = mfma32(a0, y[0], z[jt]);
-        }
-      }
-    });
-    static_for_it<0, IT>([&](auto jt_c) {
-      constexpr int jt = decltype(jt_c)::value;
-      const f32x16& zt = z[jt];
-      if (j2 < n2) {                                           // one branch on the output type per tile, not per element
-        const size_t at0 = (size_t)m * n + (size_t)(jt * 32 + 4 * h) * n2 + j2;
-        const int rows_left = n1 - (jt * 32 + 4 * h);            // rows 8 (e / 4) + e % 4 below this count exist
-        auto store_tile = [&](auto* out) __attribute__((always_inline)) {
-          typedef typename std::remove_pointer<decltype(out)>::type T;
-          if ((jt + 1) * 32 <= n1) {                              // a whole block of rows (uniform): no per-element test
-#pragma unroll
-            for (int e = 0; e < 16; ++e) out[at0 + (size_t)((8 * (e >> 2) + (e & 3)) * n2)] = (T)zt[e];
-          } else {
-#pragma unroll
-            for (int e = 0; e < 16; ++e) {
-              const int r = 8 * (e >> 2) + (e & 3);
-              if (r < rows_left) out[at0 + (size_t)(r * n2)] = (T)zt[e];
-            }
-          }
-        };
-        if (y_dtype == BTC_BF16) store_tile((__bf16*)Y);
-        else if (y_dtype == BTC_F32) store_tile((float*)Y);
-        else store_tile((_Float16*)Y);
-      }
-    });
-  }
-}
-
-template <int IT, int NP>
-static btc_status launch_mfma_np(hipStream_t q, const uint16_t* X, int M, int n1, int n2, const uint32_t* sign_bits,
-                              const float* P1, const float* P2, void* Y, int y_dtype) {
-  const int p2_bytes = (n2 >> 4) * 3 * 1024;
-  const int lds = p2_bytes + IT * 2 * IT * 3 * 1024;
-  static bool attr_set = false;              // one-time kernel attribute, not call state
-  if (!attr_set) {
-    if (hipFuncSetAttribute((const void*)transform_mfma_kernel<IT, NP>, hipFuncAttributeMaxDynamicSharedMemorySize,
-                            160 * 1024 - 256) != hipSuccess)
-      return BTC_ERR_HIP;
-    attr_set = true;
-  }
-  const int gx = (n2 + 31) / 32;
-  constexpr int NWV = mfma_waves<IT>();
-  int gy = (IT <= 2 ? 768 : 256) / gx;       // as many workgroups as stay resident; a wave walks the rows dealt to it
-  if (gy > (M + NWV - 1) / NWV) gy = (M + NWV - 1) / NWV;
-  if (gy < 1) gy = 1;
-  transform_mfma_kernel<IT, NP><<<dim3(gx, gy), 64 * NWV, lds, q>>>(X, M, n1, n2, sign_bits, P1, P2, Y, y_dtype, p2_bytes);
-  return launch_status();
-}
-
-template <int IT>
-static btc_status launch_mfma(hipStream_t q, const uint16_t* X, int M, int n1, int n2, const uint32_t* sign_bits,
-                              const float* P1, const float* P2, void* Y, int y_dtype) {
-  if (y_dtype == BTC_F32) return launch_mfma_np<IT, 3>(q, X, M, n1, n2, sign_bits, P1, P2, Y, y_dtype);
-  return launch_mfma_np<IT, 2>(q, X, M, n1, n2, sign_bits, P1, P2, Y, y_dtype);
-}
-
 }  // namespace transform
 }  // namespace btc
 
@@ -519,14 +282,16 @@ btc_status btc_transform(void* stream, const void* X, btc_dtype x_dtype, int32_t
   if (!aligned16(X) || !aligned16(sign_bits) || !aligned16(P1) || !aligned16(P2) || !aligned16(Y)) return BTC_ERR_ALIGN;
   if (X == Y) return BTC_ERR_UNSUPPORTED;    // workgroups read whole rows that others write slices of
   hipStream_t q = (hipStream_t)stream;
-  if (x_dtype == BTC_BF16 && (n2 & 15) == 0 && M >= 64) {    // prefill on the matrix cores
-    const uint16_t* Xm = (const uint16_t*)X;
-    switch ((n1 + 31) / 32) {
-      case 1: return launch_mfma<1>(q, Xm, M, n1, n2, sign_bits, P1, P2, Y, (int)y_dtype);
-      case 2: return launch_mfma<2>(q, Xm, M, n1, n2, sign_bits, P1, P2, Y, (int)y_dtype);
-      case 3: return launch_mfma<3>(q, Xm, M, n1, n2, sign_bits, P1, P2, Y, (int)y_dtype);
-      default: return launch_mfma<4>(q, Xm, M, n1, n2, sign_bits, P1, P2, Y, (int)y_dtype);
-    }
+  // The matrix cores from where the kernel above needs a second round of workgroups on (it has one per row and eight columns,
+  // and large factors leave room for one per compute unit): 108 x 128, 12 rows 10.2 against 11.3 us, 17 rows 18.6 against
+  // 11.3; 64 x 80, 24 rows 6.0 against 7.2 (fp16: 8.6), 48 rows 8.4 against 7.3 (8.7).
+  const long long vector_wgs = (long long)M * ((n2 + 7) / 8);
+  const bool many = vector_wgs > (n1 > 64 ? 256 : x_dtype == BTC_BF16 && (n2 & 1) == 0 ? 360 : 400);
+  if (many && (long long)M * n1 * n2 < (1LL << 30)) {   // (32-bit byte offsets)
+    const btc_status st = (n2 & 15) == 0  ? mfma_16(q, X, x_dtype == BTC_BF16, M, n1, n2, sign_bits, P1, P2, Y, (int)y_dtype)
+                          : (n2 & 1) == 0 ? mfma_2(q, X, x_dtype == BTC_BF16, M, n1, n2, sign_bits, P1, P2, Y, (int)y_dtype)
+                                          : mfma_1(q, X, x_dtype == BTC_BF16, M, n1, n2, sign_bits, P1, P2, Y, (int)y_dtype);
+    if (st != BTC_ERR_UNSUPPORTED) return st;
   }
   int n_cb = (n2 + kCB - 1) / kCB;
   // A few rows: one workgroup of 1024 threads per (column block, row), dot products cut in four.

@@ -243,7 +243,7 @@ btc_status btc_weight_rowsums(void* stream, const btc_shape* s, const uint32_t* 
   char* inner = (char*)workspace + aq::align256((size_t)s->in * 2) + aq::align256((size_t)s->out * 4);
   const size_t inner_bytes = btc_workspace_bytes(s, 1, 0);
   hipStream_t q = (hipStream_t)stream;
-  if (gemv_auto_uses_workspace(dims_of(*s), 1)) {
+  if (gemv_auto_uses_workspace(dims_of(*s), 1, /*y_is_f32=*/1)) {
     st = aq::zero_fill(q, inner, inner_bytes);
     if (st != BTC_OK) return st;
   }
@@ -289,7 +289,7 @@ btc_status btc_gemm_aq(void* stream, const btc_shape* s, const uint32_t* packed,
   if (st != BTC_OK) return st;
   if (M <= 16) {
     // the decode engines that park partial sums want their workspace zero-filled and hand it back that way
-    if (gemv_auto_uses_workspace(dims_of(*s), M)) {
+    if (gemv_auto_uses_workspace(dims_of(*s), M, /*y_is_f32=*/1)) {
       st = aq::zero_fill(q, inner, inner_bytes);
       if (st != BTC_OK) return st;
     }

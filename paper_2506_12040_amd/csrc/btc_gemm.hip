@@ -84,7 +84,7 @@ btc_status btc_gemm(void* stream, const btc_shape* s, const uint32_t* packed, co
   }
   // 17..64 activation rows: the same operand scheme with two or four blocks of activation rows
   // per table read, one pass over the index stream.
-  if (gemm_rows_covers(d, M) && gemm_rows_estimate_us(d, M) < decode_us)
+  if (gemm_rows_covers(d, M) && gemm_rows_estimate_us(d, M) < 1.07 * decode_us)   // (short calls last longer than its estimate says)
     return gemm_rows(q, d, packed, codebook, alpha, mu, X, is_bf16, M, Y, (int)y_dtype, workspace);
   // Few activation rows: decoding dominates, and the decode engine of btc_gemv (table entries
   // that are matrix-core operands, 16 rows per pass) is several times quicker than a 256-row tile

@@ -356,11 +356,11 @@ size_t gemm_rows_workspace_bytes(const Dims& d, int M) {
   return rows_xpart_bytes(d, pl) + (size_t)pl.n_cs * M * d.out * sizeof(float);
 }
 
-// Fitted to measurements on 2.6 .. 26 MB matrices (two launches, prologue, second pass; the index
+// Fitted to measurements on 0.1 .. 10 MB matrices (two launches, prologue, second pass; the index
 // stream; what grows with the number of activation rows).
 double gemm_rows_estimate_us(const Dims& d, int M) {
-  const double bytes = (double)d.out * d.wpr * 4;
-  return M <= 32 ? 12.3 + 0.7e-6 * bytes : M <= 48 ? 13.9 + 1.07e-6 * bytes : 15.4 + 1.48e-6 * bytes;
+  const double mb = 1e-6 * (double)d.out * d.wpr * 4;
+  return M <= 32 ? 8.9 + 1.15 * mb : M <= 48 ? 10.6 + 1.55 * mb : 12.1 + 1.7 * mb;
 }
 
 btc_status gemm_rows(hipStream_t q, const Dims& d, const uint32_t* packed, const uint32_t* codebook, const float* alpha,

@@ -5,11 +5,18 @@
 
 namespace btc {
 
-// The dispatcher's choice of engine for a shape and a number of activation rows.  Figures: microseconds of GPU time per
-// call in a captured graph, on cold copies.
-static int choose_engine(const Dims& d, int batch) {
+// The dispatcher's choice of engine for a shape, a number of activation rows and a type of output.  Figures: microseconds of
+// GPU time per call in a captured graph, on cold copies.
+//
+// The table engine rounds its entries to fp16 (2e-4 of a row of outputs), the 4-bit engine drops what lies 2^-30 below the
+// largest activation of a block (2e-5 with outlier channels); the others sum in fp32.  Behind a 16-bit output this does not
+// show.  An fp32 output shows it: there a shape keeps the arithmetic it has always had -- or better where that
+// costs nothing -- so that callers who compare or reproduce fp32 results see no change of that size.
+static int choose_engine(const Dims& d, int batch, int y_is_f32) {
   const long long bytes = (long long)d.out * d.wpr * 4;
-  if (batch > 1 && gemv_few_covers(d, batch))
+  const bool odd = (d.in & 1) != 0;
+  if (batch > 1 && gemv_few_covers(d, batch) &&
+      !(y_is_f32 && odd && (d.v == 10 || bytes >= (3LL << 20)) && lut_engine_covers(d)))
     // Several activation rows: decoding the indices is the cost, and one pass serves all the rows.  One kernel where the
     // activations fit LDS in few pieces; the engine whose column tiles meet in a second kernel where they do not
     // (4096 x 4096 at 0.9 bit, 2 / 4 / 8 / 16 rows: 6.2 / 7.1 / 8.5 / 12.2 us against 8.0 / 8.1 / 8.6 / 9.5; 16 rows of
@@ -17,14 +24,24 @@ static int choose_engine(const Dims& d, int batch) {
     return gemv_mfma_covers(d, batch) && gemv_mfma_estimate_us(d, batch) < gemv_few_estimate_us(d, batch) ? BTC_ENGINE_MFMA
                                                                                                           : BTC_ENGINE_MFMA_ONE;
   if (batch == 1) {
-    // One activation row.  Small matrices are bound by the chain of memory round trips, and the register-resident engine
-    // has the shortest one: 3.3 us up to 0.1 MB, level with the engine on the 4-bit matrix cores at 0.85 MB (4.9 us) and
-    // far behind it from there on (1.4 MB: 5.6 against 4.4, 1.9 MB: 7.7 against 4.4).  It takes even rows only.
-    if (gemv_fp4_covers(d) && (bytes >= 850000 || !expand_engine_covers(d))) return BTC_ENGINE_FP4;
+    if (gemv_fp4_covers(d)) {
+      // Large matrices, and long rows from 1 MiB on: the engine on the 4-bit matrix cores (6212 x 4032: 6.0 us, register-
+      // resident engine 12.0).
+      if (bytes >= (5LL << 19) || (bytes >= (1LL << 20) && d.nchunks >= 600)) {
+        // chunk length 9 and long rows: more steps than its waves hold operands for (1456 x 8048: 8.3 against 6.8 us)
+        return d.v == 9 && d.nchunks >= 800 && bytes < (3LL << 20) ? BTC_ENGINE_MFMA_ONE : BTC_ENGINE_FP4;
+      }
+      // Smaller ones are bound by the chain of memory round trips, and the register-resident engine has the shortest one: 3.3
+      // us up to 0.1 MB.  The lines where the two meet (4.6 us either way): 0.85 MB, 1.4 MB for rows of 420 chunks and
+      // more, which cost the 4-bit engine another step (1744 x 5680 at 0.8 bit, 1.0 MB: 5.2 against 4.5).
+      if (!y_is_f32 && (bytes >= (d.nchunks < 420 || d.v == 9 ? 850000 : 1400000) || !expand_engine_covers(d)))
+        return BTC_ENGINE_FP4;
+      if (y_is_f32 && bytes >= 1700000 && expand_engine_covers(d)) return BTC_ENGINE_MFMA_ONE;      // (4640 x 4160: 6.7 against 6.9)
+    }
     // Longer rows than that engine takes, in a large matrix: the table engine cannot use its streaming kernel there, and
     // with 10-bit indices its table leaves one workgroup per compute unit only (20595 x 28516 at 1.11 bit: 115 against 57
     // us; 74 with column tiles and a second kernel).
-    if (gemv_few_covers(d, batch) &&
+    if (gemv_few_covers(d, batch) && !(y_is_f32 && odd) &&
         ((d.b >= 9 && d.nchunks >= 2048 && bytes >= (16LL << 20)) || (d.b == 10 && bytes >= (8LL << 20))))
       return BTC_ENGINE_MFMA_ONE;
   } else if (gemm_decode_covers(d, batch) && batch * (3.5 + 1.8e-6 * bytes) > gemm_decode_estimate_us(d, batch)) {
@@ -52,7 +69,9 @@ static size_t engine_workspace_bytes(const Dims& d, int engine, int batch) {
 }
 
 // Whether btc_gemv on this shape and batch parks anything in (and expects zeros in) its workspace.
-bool gemv_auto_uses_workspace(const Dims& d, int batch) { return engine_uses_workspace(choose_engine(d, batch)); }
+bool gemv_auto_uses_workspace(const Dims& d, int batch, int y_is_f32) {
+  return engine_uses_workspace(choose_engine(d, batch, y_is_f32));
+}
 
 // One decode call through a chosen engine (engine = BTC_ENGINE_AUTO: the dispatcher's own choice).  A forced
 // engine that does not cover the shape or the batch returns BTC_ERR_UNSUPPORTED.
@@ -72,7 +91,7 @@ static btc_status gemv_dispatch(int engine, void* stream, const btc_shape* s, co
   const int y_is_f32 = y_dtype == BTC_F32;
   const size_t ysz = y_is_f32 ? 4 : 2;
 
-  if (engine == BTC_ENGINE_AUTO) engine = choose_engine(d, batch);
+  if (engine == BTC_ENGINE_AUTO) engine = choose_engine(d, batch, y_is_f32);
 
   switch (engine) {
     case BTC_ENGINE_MFMA_ONE:
@@ -175,7 +194,7 @@ btc_status btc_gemv_static(void* stream, const btc_shape* s, const uint32_t* pac
   if (st != BTC_OK) return st;
   if (batch < 1 || batch > 16) return BTC_ERR_UNSUPPORTED;
   const Dims d = dims_of(*s);
-  const int engine = choose_engine(d, batch);
+  const int engine = choose_engine(d, batch, y_dtype == BTC_F32);
   if (!engine_uses_workspace(engine))   // most single-row calls: nothing is parked anywhere
     return gemv_dispatch(engine, stream, s, packed, codebook, alpha, mu, x, batch, y, y_dtype, nullptr, 0);
   const size_t need = engine_workspace_bytes(d, engine, batch);

@@ -95,7 +95,7 @@ btc_status btc_gemm(void* stream, const btc_shape* s, const uint32_t* packed, co
     for (int m0 = 0; m0 < M; m0 += 16) {
       const int rows = M - m0 < 16 ? M - m0 : 16;
       st = gemv_mfma(q, d, packed, codebook, alpha, mu, (const char*)X + (size_t)m0 * d.in * xsz, is_bf16, rows,
-                     (char*)Y + (size_t)m0 * d.out * ysz, (int)y_dtype, workspace);
+                     (char*)Y + (size_t)m0 * d.out * ysz, (int)y_dtype, workspace, /*clear_workspace=*/0);
       if (st != BTC_OK) return st;
     }
     return BTC_OK;

@@ -735,26 +735,41 @@ __global__ __launch_bounds__(256) void decode_reduce_kernel(float* __restrict__ 
   __shared__ float red[4];
   const int m = blockIdx.y, tid = threadIdx.x;
   const size_t total = (size_t)M * out;
-  const float rs = row_sum<OP>(X, m, in, red);
-  const float sv = OP == kI8 ? ca.step[m] : 1.f, lv = OP == kI8 ? ca.lo[m] : 0.f;
-  auto finish = [&](float s, int n) {
-    const float r = alpha[n] * s + mu[n] * rs;
-    return OP == kI8 ? sv * r + lv * ca.wsum[n] : r;
-  };
   const size_t row = (size_t)m * out;
   const int n_begin = blockIdx.x * n_part, n_end = min(out, n_begin + n_part);
-  if ((out & 3) == 0) {
-    for (int n = n_begin + 4 * tid; n < n_end; n += 4 * 256) {
-      f32x4 v = {0.f, 0.f, 0.f, 0.f};
+  // Everything the first outputs need is requested before the row is added up: the call is a chain of latencies.
+  const bool vec = (out & 3) == 0;
+  const int n_first = n_begin + 4 * tid;
+  f32x4 first = {0.f, 0.f, 0.f, 0.f}, al = first, mn = first, ws = first;
+  if (vec && n_first < n_end) {
+    al = *(const f32x4*)(alpha + n_first);
+    mn = *(const f32x4*)(mu + n_first);
+    if (OP == kI8) ws = *(const f32x4*)(ca.wsum + n_first);
 #pragma unroll 4
-      for (int sp = 0; sp < splits; ++sp) {
-        f32x4* p = (f32x4*)(part + (size_t)sp * total + row + n);
-        v += *p;
-        if (clear) *p = f32x4{0.f, 0.f, 0.f, 0.f};
+    for (int sp = 0; sp < splits; ++sp) first += *(const f32x4*)(part + (size_t)sp * total + row + n_first);
+  }
+  const float rs = row_sum<OP>(X, m, in, red);
+  const float sv = OP == kI8 ? ca.step[m] : 1.f, lv = OP == kI8 ? ca.lo[m] : 0.f;
+  auto finish = [&](float s, float a, float u, float w) {
+    const float r = a * s + u * rs;
+    return OP == kI8 ? sv * r + lv * w : r;
+  };
+  if (vec) {
+    for (int n = n_first; n < n_end; n += 4 * 256) {
+      f32x4 v = first;
+      if (n != n_first) {
+        v = f32x4{0.f, 0.f, 0.f, 0.f};
+        al = *(const f32x4*)(alpha + n);
+        mn = *(const f32x4*)(mu + n);
+        if (OP == kI8) ws = *(const f32x4*)(ca.wsum + n);
+#pragma unroll 4
+        for (int sp = 0; sp < splits; ++sp) v += *(const f32x4*)(part + (size_t)sp * total + row + n);
       }
+      if (clear)
+        for (int sp = 0; sp < splits; ++sp) *(f32x4*)(part + (size_t)sp * total + row + n) = f32x4{0.f, 0.f, 0.f, 0.f};
       float r[4];
 #pragma unroll
-      for (int e = 0; e < 4; ++e) r[e] = finish(v[e], n + e);
+      for (int e = 0; e < 4; ++e) r[e] = finish(v[e], al[e], mn[e], ws[e]);
       if (y_dtype == BTC_F32) {
         *(f32x4*)((float*)Y + row + n) = f32x4{r[0], r[1], r[2], r[3]};
       } else if (y_dtype == BTC_BF16) {
@@ -773,7 +788,7 @@ __global__ __launch_bounds__(256) void decode_reduce_kernel(float* __restrict__ 
         v += *p;
         if (clear) *p = 0.f;
       }
-      const float r = finish(v, n);
+      const float r = finish(v, alpha[n], mu[n], OP == kI8 ? ca.wsum[n] : 0.f);
       if (y_dtype == BTC_F32) ((float*)Y)[row + n] = r;
       else if (y_dtype == BTC_BF16) ((__hip_bfloat16*)Y)[row + n] = __float2bfloat16(r);
       else ((__half*)Y)[row + n] = __float2half_rn(r);

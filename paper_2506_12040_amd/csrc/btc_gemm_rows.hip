@@ -379,7 +379,7 @@ btc_status gemm_rows(hipStream_t q, const Dims& d, const uint32_t* packed, const
     default: return BTC_ERR_UNSUPPORTED;
   }
   if (st != BTC_OK) return st;
-  return skinny_reduce(q, alpha, mu, part, xpart, d.out, M, pl.n_cs, 64, Y, y_dtype);
+  return skinny_reduce(q, alpha, mu, part, xpart, d.out, M, pl.n_cs, 64, Y, y_dtype, /*clear=*/0);
 }
 
 }  // namespace btc

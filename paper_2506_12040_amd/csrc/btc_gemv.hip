@@ -103,7 +103,8 @@ static btc_status gemv_dispatch(int engine, void* stream, const btc_shape* s, co
       const size_t need = gemv_mfma_workspace_bytes(d, batch);
       if (!workspace || workspace_bytes < off + need) return BTC_ERR_WORKSPACE;
       if (!aligned16(workspace)) return BTC_ERR_ALIGN;
-      return gemv_mfma(q, d, packed, codebook, alpha, mu, x, /*is_bf16=*/0, batch, y, (int)y_dtype, (char*)workspace + off);
+      return gemv_mfma(q, d, packed, codebook, alpha, mu, x, /*is_bf16=*/0, batch, y, (int)y_dtype, (char*)workspace + off,
+                       /*clear_workspace=*/1);
     }
     case BTC_ENGINE_TILED: {
       // Decoding the indices is the cost, and the matrix cores take up to 32 rows for the price of one:

@@ -32,7 +32,7 @@
 // to 4 super-groups of columns; the index words of a super-group are requested while the
 // previous one is contracted.  The column tiles of a row leave fp32 partial sums in the
 // workspace and a second, small kernel adds them, applies alpha and mu (Algorithm "Binary
-// Transformation and Compression": W_hat = alpha * B_hat + mu) and clears what it has read.
+// Transformation and Compression": W_hat = alpha * B_hat + mu) and, for btc_gemv, clears what it has read.
 #include "btc_mfma_decode.h"
 
 namespace btc {
@@ -326,7 +326,7 @@ __global__ __launch_bounds__(kWaves * 64) void gemv_mfma_kernel(
 // cost more than the second launch.)
 __global__ __launch_bounds__(256) void skinny_reduce_kernel(const float* __restrict__ alpha, const float* __restrict__ mu,
                                                             float* __restrict__ part, float* __restrict__ xpart, int out,
-                                                            int batch, int n_ct, int xstride, void* __restrict__ y, int y_dtype) {
+                                                            int batch, int n_ct, int xstride, void* __restrict__ y, int y_dtype, int clear) {
   __shared__ float4 red[3][64];
   const int nb = blockIdx.x, j = blockIdx.y, tid = threadIdx.x, lane = tid & 63, g = tid >> 6;
   const int n_end = min(out, (nb + 1) * kReduceCols);
@@ -356,7 +356,7 @@ __global__ __launch_bounds__(256) void skinny_reduce_kernel(const float* __restr
 #pragma unroll
         for (int u = 0; u < 4; ++u) {
           v.x += t[u].x; v.y += t[u].y; v.z += t[u].z; v.w += t[u].w;
-          if (ct + 4 * u < n_ct) p0[(size_t)(ct + 4 * u) * step] = make_float4(0.f, 0.f, 0.f, 0.f);
+          if (clear && ct + 4 * u < n_ct) p0[(size_t)(ct + 4 * u) * step] = make_float4(0.f, 0.f, 0.f, 0.f);
         }
       }
     }
@@ -388,7 +388,7 @@ __global__ __launch_bounds__(256) void skinny_reduce_kernel(const float* __restr
         for (int ct = 0; ct < n_ct; ++ct) {
           float* p = part + ((size_t)ct * batch + j) * out + n;
           v += *p;
-          *p = 0.f;
+          if (clear) *p = 0.f;
         }
         const float r = alpha[n] * v + mu[n] * xs;
         if (y_dtype == BTC_F32) ((float*)y)[yrow + n] = r;
@@ -398,7 +398,7 @@ __global__ __launch_bounds__(256) void skinny_reduce_kernel(const float* __restr
     }
   }
   // the row sums are read by wave 0 only, which clears them afterwards
-  if (g == 0)
+  if (clear && g == 0)
     for (int ct = lane; ct < n_ct; ct += 64) xpart[((size_t)nb * n_ct + ct) * xstride + j] = 0.f;
 }
 
@@ -481,15 +481,15 @@ double gemv_mfma_estimate_us(const Dims& d, int batch) {
 }
 
 btc_status skinny_reduce(hipStream_t q, const float* alpha, const float* mu, float* part, float* xpart, int out,
-                         int rows, int n_ct, int xstride, void* y, int y_dtype) {
+                         int rows, int n_ct, int xstride, void* y, int y_dtype, int clear) {
   const int n_rb = (out + skinny::kReduceCols - 1) / skinny::kReduceCols;
   skinny::skinny_reduce_kernel<<<dim3(n_rb, rows), 256, 0, q>>>(alpha, mu, part, xpart, out, rows, n_ct, xstride, y,
-                                                               y_dtype);
+                                                               y_dtype, clear);
   return launch_status();
 }
 
 btc_status gemv_mfma(hipStream_t q, const Dims& d, const uint32_t* packed, const uint32_t* codebook, const float* alpha,
-                     const float* mu, const void* x, int is_bf16, int batch, void* y, int y_dtype, void* workspace) {
+                     const float* mu, const void* x, int is_bf16, int batch, void* y, int y_dtype, void* workspace, int clear_workspace) {
   using namespace skinny;
   const Plan pl = make_plan(d);
   const int n_rb = (d.out + kReduceCols - 1) / kReduceCols;
@@ -508,7 +508,7 @@ btc_status gemv_mfma(hipStream_t q, const Dims& d, const uint32_t* packed, const
     default: return BTC_ERR_UNSUPPORTED;
   }
   if (st != BTC_OK) return st;
-  return skinny_reduce(q, alpha, mu, part, xpart, d.out, batch, pl.n_ct, 16, y, y_dtype);
+  return skinny_reduce(q, alpha, mu, part, xpart, d.out, batch, pl.n_ct, 16, y, y_dtype, clear_workspace);
 }
 
 }  // namespace btc

@@ -67,7 +67,7 @@ size_t gemv_mfma_workspace_bytes(const Dims& d, int batch);
 double gemv_mfma_estimate_us(const Dims& d, int batch);   // rough duration, for engine selection
 btc_status gemv_mfma(hipStream_t q, const Dims& d, const uint32_t* packed, const uint32_t* codebook,
                      const float* alpha, const float* mu, const void* x, int is_bf16, int batch, void* y,
-                     int y_dtype, void* workspace);
+                     int y_dtype, void* workspace, int clear_workspace);
 
 // The same operand scheme in one kernel (btc_gemv_few.hip): a workgroup walks all columns.
 bool gemv_few_covers(const Dims& d, int batch);
@@ -82,9 +82,9 @@ btc_status gemm_few_codes(hipStream_t q, const Dims& d, const uint32_t* packed, 
 
 // Second pass of the engines above and below: y = alpha * (sum of `n_ct` partial-sum planes
 // [n_ct][rows][out]) + mu * (sum of `n_ct` row-sum entries, one copy of [n_ct][xstride] per block of
-// 256 outputs); clears what it reads.
+// 256 outputs); with `clear` it leaves zeros behind (btc_gemv promises that to its callers).
 btc_status skinny_reduce(hipStream_t q, const float* alpha, const float* mu, float* part, float* xpart, int out,
-                         int rows, int n_ct, int xstride, void* y, int y_dtype);
+                         int rows, int n_ct, int xstride, void* y, int y_dtype, int clear);
 // 17..64 activation rows on the same operand scheme (btc_gemm_rows.hip): a workgroup keeps its
 // accumulators while it walks its share of the columns, restaging the activations per super-group.
 bool gemm_rows_covers(const Dims& d, int M);

@@ -36,10 +36,10 @@
 //    end (the other columns are products with another step's activations).  That keeps the kernel below
 //    128 registers: four waves per SIMD, which is what hides the LDS and memory latencies here.
 //  * A workgroup owns whole rows: eight column waves split the columns of a row block, their sixteen-row
-//    partial sums meet in LDS and one wave applies alpha, mu * sum(x) and stores.  Two such teams of eight
-//    waves work on two row blocks at a time and share the table, the B operands and one barrier per step
-//    of the row loop.  No workspace, no traffic between workgroups, one launch, deterministic.
-//  * Index words are requested two row blocks ahead; a row block is 16 whole rows of the stream, so
+//    partial sums of up to four row blocks meet in LDS, then one thread per row applies alpha, mu * sum(x) and
+//    stores.  Two such teams of eight waves work on two row blocks at a time and share the table, the B operands
+//    and one barrier per four steps of the row loop.  No workspace, no traffic between workgroups, one launch, deterministic.
+//  * Index words are requested a row block ahead of their staging in LDS; a row block is 16 whole rows of the stream, so
 //    the matrix is read front to back in large contiguous pieces.
 #include <hip/hip_fp16.h>
 
@@ -78,10 +78,6 @@ struct Cfg {
   static constexpr int G = 3;                               // chunks per 128-bit operand of a lane
   static constexpr int TAIL = V - 8;                        // elements of a chunk in the high word of its entry
   static constexpr int L = G * T;                           // chunks per strand
-  // Row blocks in flight per wave in registers (one more sits in LDS).  One: measured against two and three, fewer
-  // requests in flight are FASTER here (28672 x 8192: 13.9 / 14.3 / 15.2 us with 1 / 2 / 3) -- a wave's later row
-  // blocks otherwise queue in front of the blocks other waves need first.
-  static constexpr int PD = 1;
   static constexpr int ND = (L * B + 31) / 32 + 1;          // index words a lane needs per row block
   // index words of a wave's four strands inside one row, fetched as 16-byte pieces by LPR lanes per row
   static constexpr int NW = (4 * L * B + 31) / 32 + 1;
@@ -90,7 +86,8 @@ struct Cfg {
   static constexpr int NLD = (16 + RPI - 1) / RPI;          // load instructions per row block
   static constexpr int S = 4 * ((LPR + 1) | 1);             // staged row stride in words: an odd number of 16-byte
                                                             // pieces, so that the 16 rows start in 16 different banks
-  static constexpr int kRedBytes = (2 * W * 16 * 4 + W * 4 + CW * 2 * 4 + 15) & ~15;
+  // partial sums of two windows of P row blocks per team, wave sums of x, block scales
+  static constexpr int red_bytes(int p) { return (2 * p * W * 16 * 4 + W * 4 + CW * 2 * 4 + 15) & ~15; }
   static constexpr int kIdxBytes = W * 16 * S * 4;          // one staged row block per wave
   static constexpr int NSET = (T + 3) / 4;                  // B register sets
   static constexpr int kStageBytes = WIDE ? 0 : CW * NSET * kSetBytes;   // wide: the wave's index area serves first
@@ -101,13 +98,18 @@ struct Cfg {
   // and the tiles of its intermediate), which may be larger
   static constexpr int kTrBytes = ftr::Shared<GN1, GN2, CW * TEAMS * 64>::kScratchBytes;
   static constexpr int kWorkBytes = kIdxBytes + kStageBytes > kTrBytes ? kIdxBytes + kStageBytes : kTrBytes;
-  static constexpr int kRestBytes = kRedBytes + kWorkBytes + kXfBytes;
+  static constexpr int kRestBytes = red_bytes(1) + kWorkBytes + kXfBytes;
   static constexpr int C0 = (B <= 8) ? 32 : (B == 9) ? 16 : 8;  // table copies (32: no two lanes of a wave share a bank pair)
   static constexpr bool fits(int c) { return (1 << B) * c * 8 + kRestBytes <= kLdsMax; }
   static constexpr int C = (!FUSED || fits(C0)) ? C0 : (C0 >= 16 && fits(C0 / 2)) ? C0 / 2 : (C0 >= 32 && fits(C0 / 4)) ? C0 / 4 : C0;
   static constexpr int LOG2C = C == 32 ? 5 : (C == 16 ? 4 : 3);
   static constexpr int kTableBytes = (1 << B) * C * 8;
-  static constexpr int kLdsBytes = kTableBytes + kRestBytes;
+  // Row blocks of a team between two barriers: four where they fit (no launch for one decoder matrix has more on 256
+  // compute units), never at the price of table copies or of the second team.
+  static constexpr bool fits_p(int p) { return kTableBytes + kRestBytes - red_bytes(1) + red_bytes(p) <= kLdsMax; }
+  static constexpr int P = fits_p(4) ? 4 : fits_p(2) ? 2 : 1;
+  static constexpr int kRedBytes = red_bytes(P);
+  static constexpr int kLdsBytes = kTableBytes + kRestBytes - red_bytes(1) + kRedBytes;
   static_assert(V == 9 || V == 10, "three chunks per operand, tails of one or two elements");
   static_assert(B >= 7 && B <= 10, "table of at most 64 KB");
   static_assert(LPR <= 32, "at least two rows per load instruction");
@@ -214,11 +216,11 @@ __global__ __launch_bounds__(CW * TEAMS * 64) void gemv_fp4_kernel(
   static_assert(!FUSED || V == 10, "the fused prologue reads aligned pairs of activations from LDS");
   constexpr bool WIDE = K::WIDE;
   constexpr int W = K::W, G = K::G, TAIL = K::TAIL, ND = K::ND, C = K::C, L = K::L;
-  constexpr int LPR = K::LPR, RPI = K::RPI, NLD = K::NLD, S = K::S, kPD = K::PD;
+  constexpr int LPR = K::LPR, RPI = K::RPI, NLD = K::NLD, S = K::S, P = K::P;
   extern __shared__ __align__(16) unsigned char smem[];
   unsigned long long* table = (unsigned long long*)smem;                       // [2^B][C], at LDS offset 0
-  float* red = (float*)(smem + K::kTableBytes);                                // [2 phases][W][16]
-  float* sxp = red + 2 * W * 16;                                               // [W]
+  float* red = (float*)(smem + K::kTableBytes);                                // [2 windows][P][W][16]
+  float* sxp = red + 2 * P * W * 16;                                              // [W]
   int* scl = (int*)(sxp + W);                                                   // [CW][2] block scale exponents
   uint32_t* idx_all = (uint32_t*)(smem + K::kTableBytes + K::kRedBytes);       // [W][16][S]
   unsigned char* bstage_all = smem + K::kTableBytes + K::kRedBytes + K::kIdxBytes;  // [CW][NSET][2048]; wide: [W][2048]
@@ -268,13 +270,18 @@ __global__ __launch_bounds__(CW * TEAMS * 64) void gemv_fp4_kernel(
   // byte 16 (qa >> 1) + (e & 15).  The two teams share the B operands: team h prepares the items of half h.
   // FUSED: the waves that own a stage-1 tile of the transform leave the table to the others, so that their
   // matrix-core work overlaps the table build instead of following it.
-  constexpr int TW0 = FUSED ? FT_NT : 0;                     // first wave that builds the table
+  // SOLO (see below): the waves of team 1 build the table while those of team 0 prepare the activations.
+  constexpr bool SOLO = !WIDE && TEAMS == 2 && 8 * T <= 64;
+  constexpr int TW0 = FUSED ? FT_NT : SOLO ? CW : 0;         // first wave that builds the table
   constexpr int TT = (W - TW0) * 64;                         // threads that build it
-  constexpr int KPT = ((1 << B) + TT - 1) / TT;
+  constexpr int KPT = ((1 << B) + TT - 1) / TT;              // entries per thread, or
+  constexpr int TPK = (TT >> B) >= 4 ? 4 : (TT >> B) >= 2 ? 2 : 1;   // threads per entry
+  static_assert(C / 2 >= TPK && (KPT == 1 || TPK == 1), "every thread writes a pair of copies");
   const int ttid = tid - TW0 * 64;                           // this thread's number among them (negative: not one)
   uint32_t cwd[KPT];
 #pragma unroll
-  for (int i = 0; i < KPT; ++i) cwd[i] = codebook[min(max(ttid, 0) + i * TT, (1 << B) - 1)];
+  for (int i = 0; i < KPT; ++i)
+    cwd[i] = codebook[TPK > 1 ? ttid & ((1 << B) - 1) : min(max(ttid, 0) + i * TT, (1 << B) - 1)];
   unsigned char* bstage = WIDE ? (unsigned char*)(idx_all + wave * (16 * S)) : bstage_all + cw * (K::NSET * kSetBytes);
   const __amdgpu_buffer_rsrc_t rx = __builtin_amdgcn_make_buffer_rsrc((void*)x, 0, d.in * 2, kRsrcFlags);
   // With two teams, team e prepares the steps t = e, e + 2, ...: a step's B operand then carries one block
@@ -282,7 +289,6 @@ __global__ __launch_bounds__(CW * TEAMS * 64) void gemv_fp4_kernel(
   // SOLO: with at most eight steps the items of BOTH teams fit one wave (8 T <= 64 lanes), so team 0 prepares all B
   // operands of its column wave, under one block scale, and the waves of team 1 skip the conversion: half as many
   // prologue instructions on every SIMD (with three steps per team only 24 of a wave's 64 lanes had an item).
-  constexpr bool SOLO = !WIDE && TEAMS == 2 && 8 * T <= 64;
   constexpr bool SPLIT = TEAMS == 2 && !SOLO;               // the teams prepare the steps of one parity each
   const bool prep = !SOLO || team == 0;                     // (wave-uniform) this wave prepares B operands
   constexpr int n_items = WIDE ? 0 : 8 * (SPLIT ? (T + 1) / 2 : T);
@@ -425,7 +431,6 @@ __global__ __launch_bounds__(CW * TEAMS * 64) void gemv_fp4_kernel(
   // the whole byte offset is per-lane: that is the part the hardware checks against the buffer size, word
   // by word (a piece that runs past the end of the last row reads zeros)
   const uint32_t piece_off = (lrow < RPI && wd0 + 4 * lpc < d.wpr) ? (uint32_t)(wd0 + 4 * lpc) * 4u : kOob;
-  uint4 D[kPD][NLD];
   auto load_block = [&](int rb, uint4 (&dst)[NLD]) {
 #pragma unroll
     for (int j = 0; j < NLD; ++j) {
@@ -466,13 +471,14 @@ __global__ __launch_bounds__(CW * TEAMS * 64) void gemv_fp4_kernel(
   // the next entry's.
 #pragma unroll
   for (int i = 0; i < KPT; ++i) {
-    const int k = ttid + i * TT;
-    if (ttid >= 0 && k < (1 << B)) {
+    const int k = TPK > 1 ? ttid & ((1 << B) - 1) : ttid + i * TT;
+    const int part = TPK > 1 ? ttid >> B : 0;
+    if (ttid >= 0 && part < TPK && k < (1 << B)) {
       const unsigned long long ent = expand_codeword<V>(cwd[i]);
       const u32x4 two = {(uint32_t)ent, (uint32_t)(ent >> 32), (uint32_t)ent, (uint32_t)(ent >> 32)};
       u32x4* const row = (u32x4*)(table + k * C);
 #pragma unroll
-      for (int c = 0; c < C / 2; ++c) row[(c + k) & (C / 2 - 1)] = two;
+      for (int c = 0; c < C / 2 / TPK; ++c) row[(c + part * (C / 2 / TPK) + k) & (C / 2 - 1)] = two;
     }
   }
   STAMP(2);
@@ -616,26 +622,19 @@ __global__ __launch_bounds__(CW * TEAMS * 64) void gemv_fp4_kernel(
   }
   }   // prep
   STAMP(5);
-  // sum of this wave's share of the activations (every element belongs to exactly one item)
-  sx_lane = wave_sum_to_lane63(sx_lane);
-  if (lane == 63) sxp[wave] = sx_lane;
-  // the next row blocks are requested, the first one's index words go to LDS
-#pragma unroll
-  for (int u = 0; u < kPD; ++u) load_block(rb_first + (u + 1) * rb_step, D[u]);
+  // the next row block is requested, the first one's index words go to LDS
+  uint4 D[NLD];
+  load_block(rb_first + rb_step, D);
+  // The scales of the first window's rows: thread (i, team, row) finishes row `row` of the team's row block i of every
+  // window.  (All threads ask, rows past the end for the last one: under a condition the compiler would wait for the
+  // values where the paths join.)
+  const int f_row = tid & 15, f_it = tid / (16 * TEAMS), f_rb = bid + (TEAMS * f_it + ((tid >> 4) & (TEAMS - 1))) * stride;
+  auto scale_row = [&](int w0) { return min((f_rb + TEAMS * w0 * stride) * 16 + f_row, d.out - 1); };
+  float al = alpha[scale_row(0)], mm_row = mu[scale_row(0)];
   stage_block(D0);
   STAMP(6);
-  __syncthreads();   // table complete, B operands staged, sums of x stored
+  __syncthreads();   // table complete, B operands staged
   STAMP(7);
-  float sx = 0.f;
-  static_assert(W % 4 == 0 && (K::kTableBytes + 2 * W * 16 * 4) % 16 == 0, "the wave sums are read four at a time");
-#pragma unroll
-  for (int w = 0; w < W; w += 4) {   // (same order of additions in every wave)
-    const float4 v = *(const float4*)(sxp + w);
-    sx += v.x;
-    sx += v.y;
-    sx += v.z;
-    sx += v.w;
-  }
 
   // ---- per-lane constants of the read-back: lane (r, q) starts at bit ws0 + q L B of its staged row
   const uint32_t lbit = (wbit0 & 31u) + (uint32_t)(q * L) * B;
@@ -653,30 +652,23 @@ __global__ __launch_bounds__(CW * TEAMS * 64) void gemv_fp4_kernel(
     Bq[tt] = i32x8{(int)lo.x, (int)lo.y, (int)lo.z, (int)lo.w, (int)hi.x, (int)hi.y, (int)hi.z, (int)hi.w};
   }
 
-  int it = 0;
-  for (int rb0 = rb_first; rb0 < n_rb + (TEAMS - 1) * stride; rb0 += kPD * rb_step) {
-#pragma unroll
-    for (int u = 0; u < kPD; ++u) {
-      const int rb = rb0 + u * rb_step;                      // may be past the end (second team): zeros, not stored
-      if (rb - team * stride >= n_rb) break;                 // the same for both teams: they share the barriers
-      // the wave that will finish this row block asks for its scales now
-      const int fw = (it + team * (W / 2 + 1)) % W;          // rotates; the two teams' finishers differ
-      const int my_row = rb * 16 + lane;
-      const bool finishes = wave == fw && lane < 16 && rb < n_rb && my_row < d.out;
-      float al = 0.f, mm = 0.f;
-      if (finishes) {
-        al = alpha[my_row];
-        mm = mu[my_row];
-      }
-      // this row block's words from LDS; then the next one's take their place (LDS operations of a wave
-      // complete in order) and the registers are refilled with the one after those in flight
+  // sum of this wave's share of the activations (every element belongs to exactly one item): read behind the next barrier
+  sx_lane = wave_sum_to_lane63(sx_lane);
+  if (lane == 63) sxp[wave] = sx_lane;
+
+  // A wave's partial sums of up to P row blocks stay in LDS before the waves of the workgroup meet: between the barriers
+  // they run freely, one wave's LDS reads under another one's reduction.  With a barrier per row block all sixteen
+  // waves were in the same phase: 0.8 of the 1.2 us of a row block at 5120 columns passed outside the step loop.
+  for (int it = 0;; ++it) {
+    const int rb = rb_first + it * rb_step;
+    const bool last = bid + (it + 1) * rb_step >= n_rb;      // of team 0; team 1 has as many row blocks, or one less
+    if (rb < n_rb) {
+      // this row block's words from LDS
       wave_lds_order();
       uint32_t Wd[ND + 1];
 #pragma unroll
       for (int i = 0; i <= ND; ++i) Wd[i] = my_words[i];
       wave_lds_order();
-      stage_block(D[u]);
-      load_block(rb + (kPD + 1) * rb_step, D[u]);
       uint32_t R[ND];     // normalised: bit 0 is the first bit of the lane's run
 #pragma unroll
       for (int i = 0; i < ND; ++i) R[i] = __builtin_amdgcn_alignbit(Wd[i + 1], Wd[i], s0);
@@ -756,21 +748,45 @@ __global__ __launch_bounds__(CW * TEAMS * 64) void gemv_fp4_kernel(
       z *= my_scale;
       z += dpp_ror4(z);
       z += dpp_ror8(z);                                      // lane n: the sum of row 4 q + n % 4
-      float* rbuf = red + (it & 1) * (W * 16) + team * (CW * 16);
+      float* rbuf = red + (it & (2 * P - 1)) * (W * 16) + team * (CW * 16);
       if (r < 4) rbuf[cw * 16 + 4 * q + r] = z;
-      if (it < 8) STAMP(10 + 5 * it);
+      // The next row block's words take this one's place (the LDS operations of a wave complete in order) and the
+      // registers are refilled.  Behind the step loop: in front of it the first row block waits for the words of the
+      // second.  One row block in flight besides the staged one: with more, a wave's later row blocks queue in front
+      // of those that other waves need first (28672 x 8192: 13.9 / 14.3 / 15.2 us with 1 / 2 / 3).
+      if (!last) {
+        stage_block(D);
+        load_block(rb + 2 * rb_step, D);
+      }
+    }
+    if (it < 8) STAMP(10 + 5 * it);
+    if (last || (it & (P - 1)) == P - 1) {
       __syncthreads();
       if (it < 8) STAMP(11 + 5 * it);
-      if (finishes) {
+      const int w0 = it & ~(P - 1);                          // first row block of the window
+      const int f_out = (f_rb + TEAMS * w0 * stride) * 16 + f_row;
+      if (f_it < P && w0 + f_it <= it && f_out < d.out) {
+        float sx = 0.f;
+        static_assert(W % 4 == 0 && (K::kTableBytes + 2 * P * W * 16 * 4) % 16 == 0, "the wave sums are read four at a time");
+#pragma unroll
+        for (int w = 0; w < W; w += 4) {
+          const float4 v = *(const float4*)(sxp + w);
+          sx += v.x;
+          sx += v.y;
+          sx += v.z;
+          sx += v.w;
+        }
+        const float* rbuf = red + ((w0 + f_it) & (2 * P - 1)) * (W * 16) + ((tid >> 4) & (TEAMS - 1)) * (CW * 16) + f_row;
         float tot = 0.f;
 #pragma unroll
-        for (int w = 0; w < CW; ++w) tot += rbuf[w * 16 + lane];
-        const float res = al * tot + mm * sx;
-        if (y_is_f32) ((__attribute__((address_space(1))) float*)y)[my_row] = res;
-        else ((__attribute__((address_space(1))) uint16_t*)y)[my_row] = __half_as_ushort(__float2half_rn(res));
+        for (int w = 0; w < CW; ++w) tot += rbuf[w * 16];
+        const float res = al * tot + mm_row * sx;
+        if (y_is_f32) ((__attribute__((address_space(1))) float*)y)[f_out] = res;
+        else ((__attribute__((address_space(1))) uint16_t*)y)[f_out] = __half_as_ushort(__float2half_rn(res));
       }
-      if (it < 8) STAMP(12 + 5 * it);
-      ++it;
+      if (last) break;
+      al = alpha[scale_row(it + 1)];
+      mm_row = mu[scale_row(it + 1)];
     }
   }
   STAMP(63);

@@ -814,7 +814,7 @@ static btc_status launch3(hipStream_t q, const Dims& d, const void* x, int y_is_
   for (int m = 0; m < mm.count; ++m) {
     if (mm.out[m] <= 0) mm.out[m] = d.out;
     nrb[m] = (mm.out[m] + 15) / 16;
-    cap[m] = (nrb[m] + TEAMS - 1) / TEAMS;
+    cap[m] = nrb[m];            // (4096 rows on 256 compute units with one team at work each, not 128 with two: 5.2 -> 4.7 us)
     wg[m] = 1;
     ++used;
   }

@@ -39,3 +39,31 @@ def test_transform(G, oracle, n1, n2, M, kind, yd):
     y2 = _run(G, xb, kind, bits, P1, P2, y_dtype)
     others = np.arange(M) != 3
     assert np.array_equal(y2[others], y[others])
+
+
+# one or a few rows: rows of n1 past four and n2 past eight, single rows and columns, rows that start inside a word, the
+# largest factors, and workgroups of two half-waves up to thirty-two
+FEW = [
+    (1, 1, 1, "f16", "f32"), (1, 256, 3, "bf16", "f32"), (4, 9, 2, "f16", "f16"), (3, 250, 3, "bf16", "bf16"), (5, 8, 1, "f16", "f32"),
+    (128, 1, 2, "f16", "f32"), (7, 255, 3, "f16", "f32"), (33, 63, 3, "bf16", "f16"), (65, 131, 4, "bf16", "f32"),
+    (72, 104, 1, "f16", "f16"), (97, 145, 5, "f16", "bf16"), (127, 255, 2, "bf16", "f32"), (128, 256, 8, "f16", "f32"),
+]
+
+
+@pytest.mark.parametrize("n1,n2,M,kind,yd", FEW)
+def test_few_rows(G, oracle, n1, n2, M, kind, yd):
+    B = G.B
+    print(f"transform few rows n1={n1} n2={n2} M={M} {kind}->{yd}", flush=True)
+    y_dtype = {"f32": B.BTC_F32, "f16": B.BTC_F16, "bf16": B.BTC_BF16}[yd]
+    bits, P1, P2 = S.draw_transform(5 + n1 + n2, n1, n2)
+    xb = S.draw_x(np.random.default_rng(n1 + n2 + M), M, n1 * n2, kind)
+    y = _run(G, xb, kind, bits, P1, P2, y_dtype)
+    ref = oracle.transform(xb, bits, P1, P2, kind)
+    _check(y, ref, y_dtype, B, (n1, n2, M, kind, yd))
+    if yd == "f32":
+        assert np.linalg.norm(y - ref) < 2e-6 * np.linalg.norm(ref)
+    if M > 1:      # a row of infinities stays among itself
+        xb[1] = {"f16": 0x7C00, "bf16": 0x7F80}[kind]
+        y2 = _run(G, xb, kind, bits, P1, P2, y_dtype)
+        others = np.arange(M) != 1
+        assert np.array_equal(y2[others], y[others])
